@@ -189,17 +189,19 @@ itc_status literal_fit_with_work(const itc_lattice_desc* d, const void* weights,
                                  double* d_trace, int32_t* iters_done, void* work, size_t work_cap, void* stream);
 itc_status report_error(itc_status s, const char* msg);
 
-// Chamfer transform: a task is (image, strip) for the column pass and
-// (image, first row) for the row pass.
+// Chamfer transform: a task is (image, strip) for the column passes and
+// (image, first row) for the row pass and the bands.
 struct ChamferTask {
   int32_t img;
   int32_t pos;
 };
 int chamfer_rows_per_task();
+int chamfer_rows_per_band();
 hipError_t launch_chamfer(const ImageDesc& im, const void* x, float* t, int a, int b, hipStream_t s);
 hipError_t launch_chamfer_batched(const ImageDesc* d_images, const ChamferTask* d_cols, int ncols,
-                                  const ChamferTask* d_rows, int nrows, int w_max, const void* x, float* t, int a,
-                                  int b, int grid_cols, int grid_rows, hipStream_t s);
+                                  const ChamferTask* d_rows, int nrows, const ChamferTask* d_bands, int nbands,
+                                  int h_max, int w_max, const void* x, float* t, int a, int b, int grid_cols,
+                                  int grid_rows, hipStream_t s);
 int label_rows_per_task();
 hipError_t launch_label(bool f64, const ImageDesc& im, const void* x, const void* w, int M, int32_t* lab,
                         hipStream_t s);

@@ -225,13 +225,14 @@ struct itc_plan {
   int32_t* d_sched = nullptr;  // fit_begin then fit_list
   itc::GradTile* d_gtiles = nullptr;
   bool any_mx = false;  // some image runs the matrix-core convolution (4-byte aligned weights base)
-  // chamfer transform: column-pass strips and row-pass row groups
-  std::vector<itc::ChamferTask> ch_cols, ch_rows;
+  // chamfer transform: column-pass strips, row-pass row groups and bands
+  std::vector<itc::ChamferTask> ch_cols, ch_rows, ch_bands;
   bool all_u8 = true;
   int w_max = 0;
   int h_max = 0;
   itc::ChamferTask* d_ch_cols = nullptr;
   itc::ChamferTask* d_ch_rows = nullptr;
+  itc::ChamferTask* d_ch_bands = nullptr;
 };
 
 // Convolution tile lists of a plan: per class key (the VALU kernel's radius
@@ -618,6 +619,7 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
     for (int st2 = 0; st2 < im.nstrips; ++st2) p->ch_cols.push_back(itc::ChamferTask{i, st2});
     // row groups shared by the chamfer row pass and the labelling (equal heights, checked below)
     for (int r0 = 0; r0 < im.H; r0 += itc::chamfer_rows_per_task()) p->ch_rows.push_back(itc::ChamferTask{i, r0});
+    for (int r0 = 0; r0 < im.H; r0 += itc::chamfer_rows_per_band()) p->ch_bands.push_back(itc::ChamferTask{i, r0});
   }
   p->key_seg.assign(PLAN_NKEYS, 0);
   p->key_per.assign(PLAN_NKEYS, 0);
@@ -653,6 +655,10 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
   if (e == hipSuccess) e = hipMalloc(&p->d_ch_rows, sizeof(itc::ChamferTask) * p->ch_rows.size());
   if (e == hipSuccess)
     e = hipMemcpy(p->d_ch_rows, p->ch_rows.data(), sizeof(itc::ChamferTask) * p->ch_rows.size(),
+                  hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMalloc(&p->d_ch_bands, sizeof(itc::ChamferTask) * p->ch_bands.size());
+  if (e == hipSuccess)
+    e = hipMemcpy(p->d_ch_bands, p->ch_bands.data(), sizeof(itc::ChamferTask) * p->ch_bands.size(),
                   hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     itc_lattice_plan_destroy(p);
@@ -746,6 +752,7 @@ void itc_lattice_plan_destroy(itc_plan* p) {
   if (p->d_gtiles) (void)hipFree(p->d_gtiles);
   if (p->d_ch_cols) (void)hipFree(p->d_ch_cols);
   if (p->d_ch_rows) (void)hipFree(p->d_ch_rows);
+  if (p->d_ch_bands) (void)hipFree(p->d_ch_bands);
   delete p;
 }
 
@@ -1176,8 +1183,8 @@ itc_status itc_lattice_chamfer_batched(itc_plan* p, const void* weights, int32_t
   const int gc = std::min((int)p->ch_cols.size(), 16 * cus);
   const int gr = std::min((int)p->ch_rows.size(), 8 * cus);
   hipError_t e = itc::launch_chamfer_batched(p->d_images, p->d_ch_cols, (int)p->ch_cols.size(), p->d_ch_rows,
-                                             (int)p->ch_rows.size(), p->w_max, weights, t_out, a, b, gc, gr,
-                                             (hipStream_t)stream);
+                                             (int)p->ch_rows.size(), p->d_ch_bands, (int)p->ch_bands.size(),
+                                             p->h_max, p->w_max, weights, t_out, a, b, gc, gr, (hipStream_t)stream);
   if (e != hipSuccess) return device_fail(e, "batched chamfer launch");
   return ok();
 }

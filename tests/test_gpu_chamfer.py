@@ -89,6 +89,16 @@ def test_chamfer_batched(gpu_lib):
         assert np.array_equal(got, O.chamfer_transform(cases[i].img).astype(np.float32)), i
 
 
+@pytest.mark.parametrize("a,b", [(3, 4), (1, 1), (1, 2), (5, 7)])
+@pytest.mark.parametrize("H,W", [(31, 63), (32, 64), (33, 65), (64, 512), (65, 513), (96, 127), (97, 1024),
+                                 (35, 1025), (66, 2048), (34, 2049), (1024, 40), (1025, 40)])
+def test_chamfer_band_edges(gpu_lib, H, W, a, b):
+    """Sizes at the edges of the 32-row bands, the 64-column strips and the compiled widths: sparse background
+    (distances across many bands and words) and a solid foreground."""
+    for img in (rand_img(H * 4096 + W, H, W, 0.9995), np.ones((H, W), np.uint8)):
+        assert np.array_equal(gpu_chamfer(gpu_lib, img, a, b), O.chamfer_transform(img, a, b).astype(np.float32))
+
+
 def ragged_batch_images():
     """300 binary images: ragged widths around the 64-column strips, single rows and columns, all foreground,
     all background."""
