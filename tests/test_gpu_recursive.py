@@ -60,6 +60,23 @@ def test_recursive_maps(gpu_lib, name, build, sigma, scale):
             assert torch.all(gpu_lib.panel_view(flat[i * n:(i + 1) * n], H, full)[:, W:] == 0)
 
 
+# sigma = 4: lines of W + 26 and H + 26 entries around the compiled segment lengths (64 segments of 7, 13, 19, 25,
+# 35 and 39 entries along rows, 48 of 8, 16, 25, 34, 45 and 52 along columns) and past the longest of each; one and
+# two S_X row groups; widths around the 8-column runs of the column pass
+@pytest.mark.parametrize("H,W,dt", [(358, 422, np.uint8), (359, 423, np.float32), (742, 806, np.uint8), (743, 807, np.uint8),
+                                    (17, 1190, np.uint8), (66, 1191, np.uint8), (1174, 15, np.float64), (1175, 18, np.uint8),
+                                    (33, 2214, np.uint8), (1606, 9, np.uint8), (1607, 8, np.uint8), (2134, 31, np.uint8),
+                                    (2135, 16, np.uint8), (2470, 33, np.uint8), (2471, 33, np.uint8), (34, 2470, np.uint8),
+                                    (35, 2471, np.uint8), (64, 64, np.float64), (65, 63, np.float64), (129, 1, np.uint8)])
+def test_recursive_line_lengths(gpu_lib, H, W, dt):
+    img = (np.random.default_rng(H * 4096 + W).uniform(size=(H, W)) * (255 if dt == np.uint8 else 1)).astype(dt)
+    _, got, sx = gpu_rec(gpu_lib, img, 4.0, 0.5)
+    A, Mu, Mv, sx_ref = O.recursive_maps(img.astype(np.float64) * 0.5, 4.0)
+    for g, r in zip(got, (A, Mu, Mv)):
+        assert normwise(g, r) <= 1e-6
+    assert sx == pytest.approx(sx_ref, rel=1e-6)
+
+
 def test_recursive_pitch(gpu_lib):
     img = (np.random.default_rng(3).uniform(size=(45, 70)) < 0.4).astype(np.uint8)
     _, got, _ = gpu_rec(gpu_lib, img, 5.0, pitch=128)
