@@ -202,11 +202,11 @@ hipError_t launch_chamfer_batched(const ImageDesc* d_images, const ChamferTask* 
                                   const ChamferTask* d_rows, int nrows, const ChamferTask* d_bands, int nbands,
                                   int h_max, int w_max, const void* x, float* t, int a, int b, int grid_cols,
                                   int grid_rows, hipStream_t s);
-int label_rows_per_task();
+int label_rows_per_band();
 hipError_t launch_label(bool f64, const ImageDesc& im, const void* x, const void* w, int M, int32_t* lab,
                         hipStream_t s);
-hipError_t launch_label_batched(const ImageDesc* d_images, const ChamferTask* d_tasks, int ntasks, int m_max,
-                                const void* x, const void* w, int32_t* lab, int grid, hipStream_t s);
+hipError_t launch_label_batched(const ImageDesc* d_images, const ChamferTask* d_bands, int nbands, int m_max,
+                                const void* x, const void* w, int32_t* lab, hipStream_t s);
 
 struct FitArgs {
   const void* maps;      // batch base of maps

@@ -617,8 +617,8 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
     p->w_max = std::max(p->w_max, im.W);
     p->h_max = std::max(p->h_max, im.H);
     for (int st2 = 0; st2 < im.nstrips; ++st2) p->ch_cols.push_back(itc::ChamferTask{i, st2});
-    // row groups shared by the chamfer row pass and the labelling (equal heights, checked below)
     for (int r0 = 0; r0 < im.H; r0 += itc::chamfer_rows_per_task()) p->ch_rows.push_back(itc::ChamferTask{i, r0});
+    // bands of the chamfer transform and of the labelling (equal heights, checked at the call)
     for (int r0 = 0; r0 < im.H; r0 += itc::chamfer_rows_per_band()) p->ch_bands.push_back(itc::ChamferTask{i, r0});
   }
   p->key_seg.assign(PLAN_NKEYS, 0);
@@ -955,12 +955,10 @@ itc_status itc_lattice_label_batched(itc_plan* p, const void* weights, const voi
                                      void* stream) {
   TraceRange trace_range("itc_lattice_label_batched");
   if (!p || !weights || !w || !labels) return fail(ITC_E_NULL, "plan, weights, w and labels must be non-NULL");
-  if (itc::label_rows_per_task() != itc::chamfer_rows_per_task())
-    return fail(ITC_E_DEVICE, "row groups of the labelling and the chamfer pass differ");
-  const int cus = device_cus();
-  const int grid = std::min((int)p->ch_rows.size(), 8 * cus);
-  hipError_t e = itc::launch_label_batched(p->d_images, p->d_ch_rows, (int)p->ch_rows.size(), p->m_max, weights, w,
-                                           labels, grid, (hipStream_t)stream);
+  if (itc::label_rows_per_band() != itc::chamfer_rows_per_band())
+    return fail(ITC_E_DEVICE, "bands of the labelling and the chamfer transform differ");
+  hipError_t e = itc::launch_label_batched(p->d_images, p->d_ch_bands, (int)p->ch_bands.size(), p->m_max, weights, w,
+                                           labels, (hipStream_t)stream);
   if (e != hipSuccess) return device_fail(e, "batched labelling launch");
   return ok();
 }

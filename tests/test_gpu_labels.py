@@ -41,6 +41,29 @@ def test_ties_and_max_codebook(gpu_lib):
     assert np.array_equal(gpu_label(gpu_lib, img, Wm), O.label_pixels(img, Wm))
 
 
+@pytest.mark.parametrize("H,W,pitch,M", [(1, 1, 1, 1), (15, 31, 31, 63), (16, 32, 32, 64), (17, 33, 36, 65), (33, 130, 130, 129),
+                                         (31, 127, 129, 200), (48, 128, 131, 1024)])
+@pytest.mark.parametrize("dt", [np.uint8, np.float32, np.float64])
+def test_tile_edges(gpu_lib, H, W, pitch, M, dt):
+    """Sizes at the edges of the 16 x 32 tiles and of the 64-codevector passes, aligned and unaligned rows, and
+    columns past the width left as they were; codevectors far off the lattice, infinite and NaN ones."""
+    rng = np.random.default_rng(H * 1000 + W + M)
+    buf = np.zeros((H, pitch), dt)
+    buf[:, :W] = (rng.uniform(size=(H, W)) < 0.6) * (200 if dt == np.uint8 else 1)
+    for bad in (None, 0, M - 1):
+        Wc = rng.uniform(-20, max(H, W) + 20, (M, 2)).astype(np.float32).astype(np.float64)
+        Wc[M // 2] = (1e30, -1e25)
+        if bad is not None:
+            Wc[bad] = (np.nan, 3.0) if bad == 0 else (np.inf, 2.0)
+        out = torch.full((H, pitch), -7, dtype=torch.int32, device="cuda")
+        gpu_lib.label(torch.from_numpy(buf).cuda()[:, :W], torch.from_numpy(Wc).cuda(), out=out)
+        got = out.cpu().numpy()
+        with np.errstate(invalid="ignore"):
+            ref = O.label_pixels(buf[:, :W], Wc) if bad != 0 else np.where(buf[:, :W] > 0, 0, -1)
+        assert np.array_equal(got[:, :W], ref)
+        assert (got[:, W:] == -7).all()
+
+
 def test_batched_segments(gpu_lib):
     """Fitted codebooks of 32 silhouettes: batched labels equal per-image labels; two against the oracle."""
     cases = S.config3_cases(indices=range(32))
