@@ -14,7 +14,17 @@
 // per-(codevector, wave) slot in LDS, and the owner adds the four slots in
 // wave order. S_XW = sum_k A_k and S_W = sum_k C_k are reduced in FP64 in a
 // fixed order, so results are bitwise reproducible and identical between the
-// single-image and the batched launch.
+// single-image and the batched launch. Every wave reduces its own A_k and its
+// own pair terms before the barrier that ends the pair phase, so one barrier
+// serves the slots and both sums and a second one the new codebook.
+//
+// A codebook of at most FIT_SMALL codevectors is one wave's work (fit_small):
+// P = 2 .. 16 lanes share a codevector and keep it, no barrier at all. A sweep is
+// a chain of latencies there: FIT_SMALL_FIGURES
+//
+// The D trace needs three FP64 logarithms a sweep (0.4 us on the chain); 64
+// sweeps' sums wait in the lanes of a wave, which then takes the logarithms of
+// all of them at once.
 //
 // Precision: codevector positions are FP64 whatever the map type (with FP32
 // coordinates the rounding of w, 2.4e-4 px near u = 2048, accumulated over
@@ -112,10 +122,11 @@ __device__ __forceinline__ void pair_blocks(const V2<T>* __restrict__ col, int n
 // Sums over j = p, p + P, .. (steps [u0, u1) in units of four) of the
 // Gaussian terms of codevector k, then over the P lanes of each codevector.
 template <typename T, int P>
-__device__ __forceinline__ void pair_chunk(const V2<T>* __restrict__ Wh, int k, int p, int u0, int u1, T& C, T& Cu,
-                                           T& Cv) {
+__device__ __forceinline__ void pair_chunk(const V2<T>* __restrict__ Wh, int k, int p, int u0, int u1, T& Cl, T& C,
+                                           T& Cu, T& Cv) {
   const V2<T> hk = Wh[k];
   pair_blocks<T, P>(Wh + p + u0 * 4 * P, u1 - u0, hk.u, hk.v, C, Cu, Cv);
+  Cl = C;  // this lane's share
   C = group_sum<P>(C);
   Cu = group_sum<P>(Cu);
   Cv = group_sum<P>(Cv);
@@ -142,14 +153,20 @@ __device__ __forceinline__ int chunk_lg(int M, int k0, int& size) {
   return 6 - ((rem & (rem - 1)) ? hb + 1 : hb);
 }
 
-// The pair phase of one sweep: wave `wave` walks its share of the chunk steps
-// and writes each visited codevector's sums to part[(k * 4 + wave) * 3 + 0..2].
-template <typename T>
-__device__ __forceinline__ void pair_phase(const V2<T>* __restrict__ Wh, T* __restrict__ part, int M, int wave,
-                                           int lane) {
+// Steps of all chunks, in units of four.
+__device__ __forceinline__ int pair_units(int M) {
   int units = 0;
   for (int k0 = 0, size = 0; k0 < M; k0 += size) units += chunk_units(M, chunk_lg(M, k0, size));
-  const int ua = units * wave / FIT_WAVES, ub = units * (wave + 1) / FIT_WAVES;
+  return units;
+}
+
+// The pair phase of one sweep: wave `wave` walks its share [ua, ub) of the
+// chunk steps and writes each visited codevector's sums to
+// part[(k * 4 + wave) * 3 + 0..2]. Returns this lane's sum of its C terms.
+template <typename T>
+__device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, T* __restrict__ part, int M, int ua, int ub,
+                                             int wave, int lane) {
+  double csum = 0.0;
   int cu0 = 0, k0 = 0;
   while (k0 < M && cu0 < ub) {  // uniform
     int size = 0;
@@ -159,17 +176,18 @@ __device__ __forceinline__ void pair_phase(const V2<T>* __restrict__ Wh, T* __re
     if (s0 < s1) {
       const int k = k0 + (lane >> lg), p = lane & ((1 << lg) - 1);
       const int u0 = s0 - cu0, u1 = s1 - cu0;
-      T C = 0, Cu = 0, Cv = 0;
+      T Cl = 0, C = 0, Cu = 0, Cv = 0;
       switch (lg) {
-        case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        default: pair_chunk<T, 64>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        default: pair_chunk<T, 64>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
       }
-      if (p == 0 && k < k0 + size) {  // lanes past the chunk read padding and are idle
+      if (k < k0 + size) csum += (double)Cl;  // lanes past the chunk read padding and are idle
+      if (p == 0 && k < k0 + size) {
         T* dst = part + ((size_t)k * FIT_WAVES + wave) * 3;
         dst[0] = C;
         dst[1] = Cu;
@@ -179,6 +197,7 @@ __device__ __forceinline__ void pair_phase(const V2<T>* __restrict__ Wh, T* __re
     cu0 += nu;
     k0 += size;
   }
+  return csum;
 }
 
 struct FitImageArgs {
@@ -196,7 +215,224 @@ struct FitImageArgs {
   const double* grad_d;  // dL/dD (one double), gradient mode only
 };
 
-template <typename T, int MAXPASS>
+// The lattice cell that a codevector was last read in (key -2: none yet), with
+// the corner values of A, M_u and M_v: they stay in registers until the
+// codevector enters another cell (near convergence it rarely does), so the maps
+// are read again only then.
+template <typename T>
+struct Cell {
+  int key = -2;
+  T a[4] = {}, mu[4] = {}, mv[4] = {};
+};
+
+struct CellMaps {
+  rsrc_t res;
+  uint32_t planeb;
+  int H, W;
+};
+
+// The cell of (u, v) (ok: a codevector is there): its fractions, and its corner
+// values if it is another one than before. Off-lattice corners load at an offset
+// past the end of the maps, which reads 0. The loads are issued here and
+// consumed by cell_read.
+template <typename T>
+__device__ __forceinline__ void cell_fetch(Cell<T>& c, const CellMaps& m, double u, double v, bool ok, T& fu, T& fv) {
+  const bool inside = ok && u > -1.0 && u < (double)m.H && v > -1.0 && v < (double)m.W;
+  const double fu0 = inside ? floor(u) : 0.0, fv0 = inside ? floor(v) : 0.0;
+  const int i0 = (int)fu0, j0 = (int)fv0;
+  fu = (T)(u - fu0);
+  fv = (T)(v - fv0);
+  const int key = inside ? (i0 + 1) * (m.W + 2) + (j0 + 1) : -1;
+  if (key != c.key) {
+    c.key = key;
+    const bool r0 = inside && i0 >= 0, r1 = inside && i0 + 1 < m.H;
+    const bool c0 = j0 >= 0, c1 = j0 + 1 < m.W;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int di = q >> 1, dj = q & 1;
+      const bool in = (di ? r1 : r0) && (dj ? c1 : c0);
+      const uint32_t off = in ? (uint32_t)map_index(m.H, i0 + di, j0 + dj) * (uint32_t)sizeof(T) : FIT_OOB;
+      c.a[q] = buf_load<T>(m.res, off, 0);
+      c.mu[q] = buf_load<T>(m.res, off, m.planeb);
+      c.mv[q] = buf_load<T>(m.res, off, 2 * m.planeb);
+    }
+  }
+}
+
+// Bilinear combination: A = sum_c b_c A(c), g = sum_c b_c ((c - w_k) A(c) - M(c)).
+template <typename T>
+__device__ __forceinline__ void cell_read(const Cell<T>& c, T fu, T fv, T& A, T& gu, T& gv) {
+  A = gu = gv = (T)0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int di = q >> 1, dj = q & 1;
+    const T b = (di ? fu : (T)1 - fu) * (dj ? fv : (T)1 - fv);
+    A = fma_t(b, c.a[q], A);
+    gu = fma_t(b, fma_t((T)di - fu, c.a[q], -c.mu[q]), gu);
+    gv = fma_t(b, fma_t((T)dj - fv, c.a[q], -c.mv[q]), gv);
+  }
+}
+
+// Slope of the bilinear interpolant of A: d/du and d/dv of sum_c b_c A(c),
+// corners c = (di, dj) in (0,0),(0,1),(1,0),(1,1).
+template <typename T>
+__device__ __forceinline__ void cell_slope(const Cell<T>& c, T fu, T fv, T& du, T& dv) {
+  du = ((T)1 - fv) * (c.a[2] - c.a[0]) + fv * (c.a[3] - c.a[1]);
+  dv = ((T)1 - fu) * (c.a[1] - c.a[0]) + fu * (c.a[3] - c.a[2]);
+}
+
+// c / s (E = E' / s), in the map type.
+template <typename T>
+__device__ __forceinline__ T repulsion(double S_XW, double S_W, double s) {
+  if constexpr (sizeof(T) == 4)
+    return (T)S_XW * recip((T)S_W * (T)s);
+  else
+    return (T)(S_XW / S_W / s);
+}
+
+// D of eq. (1) from the sums.
+__device__ __forceinline__ double divergence_of(double S_XW, double S_W, double s_x) {
+  return log(S_W) + log(s_x) - 2.0 * log(S_XW);
+}
+
+// The D trace of one wave: lane t mod 64 keeps the sums of sweep t, and 64
+// sweeps (or what is left at the end) take their logarithms together.
+struct TraceRing {
+  double sxw = 1.0, sw = 1.0;
+  __device__ __forceinline__ void put(int t, double S_XW, double S_W, double s_x, double* d_trace, int lane) {
+    if (lane == (t & 63)) {
+      sxw = S_XW;
+      sw = S_W;
+    }
+    if ((t & 63) == 63) flush(t, s_x, d_trace, lane);
+  }
+  // the sweeps t & ~63 .. t
+  __device__ __forceinline__ void flush(int t, double s_x, double* d_trace, int lane) {
+    if (lane <= (t & 63)) d_trace[(t & ~63) + lane] = divergence_of(sxw, sw, s_x);
+  }
+};
+
+// Codebooks of at most FIT_SMALL codevectors, one wave: lanes k P .. k P + P - 1
+// hold codevector k (the same values in each) and take the pair terms of j = p,
+// p + P, .. (p their place among the P), M <= 64 / P. Wh: 64 entries in LDS, padded
+// with FIT_FAR.
+constexpr int FIT_SMALL = 32;
+
+template <typename T, int P, bool TRACE>
+__device__ void fit_small(const ImageDesc& im, const FitImageArgs& a, V2<T>* __restrict__ Wh) {
+  constexpr int NJ = 64 / P / P > 1 ? 64 / P / P : 1;  // pair terms of a lane
+  const int M = im.M, lane = threadIdx.x & 63, k = lane / P, p = lane % P;
+  const bool own = k < M, lead = own && p == 0;
+  const double s = sqrt(1.4426950408889634 / (2.0 * im.sigma * im.sigma));
+  const double cu = 0.5 * im.H, cv = 0.5 * im.W;
+  auto lds_pos = [&](double u, double v) { return V2<T>{(T)(s * (u - cu)), (T)(s * (v - cv))}; };
+  const V2<T>* w_in = reinterpret_cast<const V2<T>*>(a.w_init) + im.w_off;
+  double wu = 0.0, wv = 0.0;
+  if (own) {
+    const V2<T> w = w_in[k];
+    wu = (double)w.u;
+    wv = (double)w.v;
+  }
+  V2<T> h = own ? lds_pos(wu, wv) : V2<T>{(T)FIT_FAR, (T)FIT_FAR};
+  // entries past 64 / P are padding for the lanes of the last block
+  Wh[lane] = V2<T>{(T)FIT_FAR, (T)FIT_FAR};
+  __builtin_amdgcn_wave_barrier();
+  if (lead) Wh[k] = h;
+  __builtin_amdgcn_wave_barrier();
+
+  CellMaps cm;
+  cm.planeb = (uint32_t)(im.plane * (int64_t)sizeof(T));
+  cm.res = make_rsrc(a.mbase + im.map_off, 3u * cm.planeb);
+  cm.H = im.H;
+  cm.W = im.W;
+  const bool need_d = a.d_trace != nullptr || a.d_out != nullptr || a.status != nullptr;
+  Cell<T> cell;
+  TraceRing ring;
+  bool stop = false;
+  int32_t flags = 0;
+  int t = 0;
+  for (;; ++t) {
+    const bool last = (t == im.iters) || stop;
+    if (last && !need_d && !a.grad_w) break;
+    T fu, fv;
+    cell_fetch(cell, cm, wu, wv, own, fu, fv);
+    // ---- codebook terms ----
+    V2<T> x[NJ];
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) x[i] = Wh[p + P * i];
+    T C[2] = {}, Eu[2] = {}, Ev[2] = {};
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
+      if (i > 0 && P * i >= M) break;  // uniform: padding only
+      const T du = x[i].u - h.u, dv = x[i].v - h.v;
+      const T e = exp2_neg(fma_t(du, du, dv * dv));
+      C[i & 1] += e;
+      Eu[i & 1] = fma_t(e, du, Eu[i & 1]);
+      Ev[i & 1] = fma_t(e, dv, Ev[i & 1]);
+    }
+    const T Cl = C[0] + C[1];
+    const T Euk = group_sum<P>(Eu[0] + Eu[1]), Evk = group_sum<P>(Ev[0] + Ev[1]);
+    // ---- data terms, sums ----
+    T A, gu, gv;
+    cell_read(cell, fu, fv, A, gu, gv);
+    double S_XW = lead ? (double)A : 0.0, S_W = own ? (double)Cl : 0.0;
+    wave_sum2(S_XW, S_W);
+    // non-finite sums (non-finite weights or maps) end the fit at this codebook
+    const bool sums_ok = isfinite(S_XW) && isfinite(S_W);  // uniform
+    const bool final_eval = last || !sums_ok;
+    if (!sums_ok) flags |= FIT_STATUS_SUMS;
+    if (final_eval && (a.d_out || a.status)) {
+      const double D = divergence_of(S_XW, S_W, a.s_x);
+      if (!isfinite(D)) flags |= FIT_STATUS_D;
+      if (lane == 0 && a.d_out) *a.d_out = D;
+    }
+    if constexpr (TRACE) {
+      if (a.d_trace) {
+        ring.put(t, S_XW, S_W, a.s_x, a.d_trace, lane);
+        if (final_eval && (t & 63) != 63) ring.flush(t, a.s_x, a.d_trace, lane);
+      }
+    }
+    if (a.grad_w) {  // adjoint of D at this codebook (eq. (1) differentiated through the reads)
+      const double gd = *a.grad_d;
+      const T ca = (T)(-2.0 * gd / S_XW);
+      const T cb = (T)(2.0 * gd / (im.sigma * im.sigma * S_W) / s);  // E = E'/s
+      V2<T>* gw = reinterpret_cast<V2<T>*>(a.grad_w) + im.w_off;
+      T dAu, dAv;
+      cell_slope(cell, fu, fv, dAu, dAv);
+      if (lead) gw[k] = V2<T>{fma_t(ca, dAu, cb * Euk), fma_t(ca, dAv, cb * Evk)};
+      break;
+    }
+    if (final_eval) break;
+    // ---- Jacobi update ----
+    const T cs = repulsion<T>(S_XW, S_W, s);
+    float step = 0.0f;
+    if (own && A != (T)0) {
+      const T inv = recip(A);
+      const T du = (gu - cs * Euk) * inv;
+      const T dv = (gv - cs * Evk) * inv;
+      if (!isfinite(du) || !isfinite(dv)) flags |= FIT_STATUS_W;
+      wu += (double)du;
+      wv += (double)dv;
+      if (a.theta >= 0.0) step = (float)sqrt((double)du * du + (double)dv * dv);
+      h = lds_pos(wu, wv);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lead) Wh[k] = h;
+    __builtin_amdgcn_wave_barrier();
+    if (a.theta >= 0.0) stop = (double)wave_max_nonneg(step) <= a.theta;
+  }
+  if (a.write_w && lead) {
+    V2<T>* w_o = reinterpret_cast<V2<T>*>(a.w_out) + im.w_off;
+    w_o[k] = V2<T>{(T)wu, (T)wv};
+  }
+  if (lane == 0 && a.iters_done) *a.iters_done = t;
+  if (a.status) {
+    const bool any_w = __any((flags & FIT_STATUS_W) != 0);
+    if (lane == 0) *a.status = (flags & ~FIT_STATUS_W) | (any_w ? FIT_STATUS_W : 0);
+  }
+}
+
+template <typename T, int MAXPASS, bool TRACE>
 __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem) {
   const int M = im.M;
   const int WL = fit_codebook_len(M);
@@ -210,6 +446,20 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
   const int npass = fit_passes(M);
   using Q2 = V2<T>;
   Q2* Wh = reinterpret_cast<Q2*>(smem);  // centred scaled positions [WL]
+  if (M <= FIT_SMALL) {  // uniform
+    if (wave == 0) {
+      if (M > 16)
+        fit_small<T, 2, TRACE>(im, a, Wh);
+      else if (M > 8)
+        fit_small<T, 4, TRACE>(im, a, Wh);
+      else if (M > 4)
+        fit_small<T, 8, TRACE>(im, a, Wh);
+      else
+        fit_small<T, 16, TRACE>(im, a, Wh);
+    }
+    __syncthreads();  // shared memory is reused by the next image
+    return;
+  }
   T* part = reinterpret_cast<T*>(smem + (size_t)WL * sizeof(P2));  // [M][4 waves][3]
   double* red = reinterpret_cast<double*>(smem + (size_t)WL * sizeof(P2) +
                                           ((size_t)M * FIT_WAVES * 3 * sizeof(T) + 7) / 8 * 8);  // [4 waves][2]
@@ -244,19 +494,15 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
   for (int i = tid; i < M * FIT_WAVES * 3; i += FIT_NT) part[i] = (T)0;
   __syncthreads();
 
-  const int H = im.H, W = im.W;
-  const uint32_t planeb = (uint32_t)(im.plane * (int64_t)sizeof(T));
-  const rsrc_t mres = make_rsrc(a.mbase + im.map_off, 3u * planeb);
+  CellMaps cm;
+  cm.planeb = (uint32_t)(im.plane * (int64_t)sizeof(T));
+  cm.res = make_rsrc(a.mbase + im.map_off, 3u * cm.planeb);
+  cm.H = im.H;
+  cm.W = im.W;
   const bool need_d = a.d_trace != nullptr || a.d_out != nullptr || a.status != nullptr;
-  // corner values of the cell each owned codevector was last read in (key -2: none yet)
-  int cell[MAXPASS];
-  T cav[MAXPASS][4], cmu[MAXPASS][4], cmv[MAXPASS][4];
-#pragma unroll
-  for (int ps = 0; ps < MAXPASS; ++ps) {
-    cell[ps] = -2;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cav[ps][c] = cmu[ps][c] = cmv[ps][c] = (T)0;
-  }
+  const int units = pair_units(M), ua = units * wave / FIT_WAVES, ub = units * (wave + 1) / FIT_WAVES;
+  Cell<T> cell[MAXPASS];
+  TraceRing ring;
 
   bool stop = false;
   int32_t flags = 0;   // status bits (uniform except FIT_STATUS_W, combined at the end)
@@ -265,90 +511,29 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     const bool last = (t == im.iters) || stop;
     if (last && !need_d && !a.grad_w) break;
 
-    // ---- data terms: bilinear read of A, M_u, M_v at w_k. The 12 corner
-    // values of the lattice cell holding w_k stay in registers until w_k
-    // enters another cell (near convergence it rarely does), so the maps are
-    // read again only then. The loads are issued before the pair phase and
-    // consumed after it, which hides their latency. Off-lattice corners load
-    // at an offset past the end of the maps, which reads 0.
+    // ---- data terms: bilinear read of A, M_u, M_v at w_k (the loads are issued
+    // before the pair phase and consumed after it, which hides their latency) ----
     T fu[MAXPASS], fv[MAXPASS];
 #pragma unroll
     for (int ps = 0; ps < MAXPASS; ++ps) {
       fu[ps] = fv[ps] = (T)0;
-      if (ps < npass) {
-        const int k = ps * FIT_NT + tid;
-        const double uk = wu[ps], vk = wv[ps];
-        const bool inside = k < M && uk > -1.0 && uk < (double)H && vk > -1.0 && vk < (double)W;
-        const double fu0 = inside ? floor(uk) : 0.0, fv0 = inside ? floor(vk) : 0.0;
-        const int i0 = (int)fu0, j0 = (int)fv0;
-        fu[ps] = (T)(uk - fu0);
-        fv[ps] = (T)(vk - fv0);
-        const int key = inside ? (i0 + 1) * (W + 2) + (j0 + 1) : -1;
-        if (key != cell[ps]) {
-          cell[ps] = key;
-          const bool r0 = inside && i0 >= 0, r1 = inside && i0 + 1 < H;
-          const bool c0 = j0 >= 0, c1 = j0 + 1 < W;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int di = c >> 1, dj = c & 1;
-            const bool ok = (di ? r1 : r0) && (dj ? c1 : c0);
-            const uint32_t off = ok ? (uint32_t)map_index(H, i0 + di, j0 + dj) * (uint32_t)sizeof(T) : FIT_OOB;
-            cav[ps][c] = buf_load<T>(mres, off, 0);
-            cmu[ps][c] = buf_load<T>(mres, off, planeb);
-            cmv[ps][c] = buf_load<T>(mres, off, 2 * planeb);
-          }
-        }
-      }
+      if (ps < npass) cell_fetch(cell[ps], cm, wu[ps], wv[ps], ps * FIT_NT + tid < M, fu[ps], fv[ps]);
     }
 
     // ---- codebook terms of every codevector (scaled coordinates) ----
-    pair_phase<T>(Wh, part, M, wave, lane);
-    __syncthreads();
+    double sw = pair_phase<T>(Wh, part, M, ua, ub, wave, lane);
 
-    T Ak[MAXPASS], gu[MAXPASS], gv[MAXPASS], Eu[MAXPASS], Ev[MAXPASS];
-    T dAu[MAXPASS], dAv[MAXPASS];  // slope of the bilinear interpolant of A at w_k
-    double sxw = 0.0, sw = 0.0;
+    // ---- A_k and g_k of the owned codevectors; this wave's shares of S_XW and S_W in FP64 ----
+    T Ak[MAXPASS], gu[MAXPASS], gv[MAXPASS];
+    double sxw = 0.0;
 #pragma unroll
     for (int ps = 0; ps < MAXPASS; ++ps) {
-      Ak[ps] = gu[ps] = gv[ps] = Eu[ps] = Ev[ps] = dAu[ps] = dAv[ps] = (T)0;
-      const int k = ps * FIT_NT + tid;
-      if (ps < npass && k < M) {
-        // the four waves' sums, in wave order
-        const T* src = part + (size_t)k * FIT_WAVES * 3;
-        T C = src[0], Cu = src[1], Cv = src[2];
-#pragma unroll
-        for (int w = 1; w < FIT_WAVES; ++w) {
-          C += src[3 * w];
-          Cu += src[3 * w + 1];
-          Cv += src[3 * w + 2];
-        }
-        const T* av = cav[ps];
-        const T* mu = cmu[ps];
-        const T* mv = cmv[ps];
-        // bilinear combination: A = sum_c b_c A(c), g = sum_c b_c ((c - w_k) A(c) - M(c))
-        const T fuk = fu[ps], fvk = fv[ps];
-        T A = 0, Gu = 0, Gv = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int di = c >> 1, dj = c & 1;
-          const T b = (di ? fuk : (T)1 - fuk) * (dj ? fvk : (T)1 - fvk);
-          A = fma_t(b, av[c], A);
-          Gu = fma_t(b, fma_t((T)di - fuk, av[c], -mu[c]), Gu);
-          Gv = fma_t(b, fma_t((T)dj - fvk, av[c], -mv[c]), Gv);
-        }
-        // d/du and d/dv of sum_c b_c A(c): corners c = (di, dj) in (0,0),(0,1),(1,0),(1,1)
-        dAu[ps] = ((T)1 - fvk) * (av[2] - av[0]) + fvk * (av[3] - av[1]);
-        dAv[ps] = ((T)1 - fuk) * (av[1] - av[0]) + fuk * (av[3] - av[2]);
-        Ak[ps] = A;
-        gu[ps] = Gu;
-        gv[ps] = Gv;
-        Eu[ps] = Cu;
-        Ev[ps] = Cv;
-        sxw += (double)A;
-        sw += (double)C;
+      Ak[ps] = gu[ps] = gv[ps] = (T)0;
+      if (ps < npass && ps * FIT_NT + tid < M) {
+        cell_read(cell[ps], fu[ps], fv[ps], Ak[ps], gu[ps], gv[ps]);
+        sxw += (double)Ak[ps];
       }
     }
-    // ---- S_XW, S_W: fixed-order block reduction in FP64 ----
     wave_sum2(sxw, sw);
     if (lane == 0) {
       red[2 * wave] = sxw;
@@ -365,12 +550,28 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     const bool sums_ok = isfinite(S_XW) && isfinite(S_W);  // uniform
     const bool final_eval = last || !sums_ok;
     if (!sums_ok) flags |= FIT_STATUS_SUMS;
-    if (tid == 0 && (a.d_trace || (final_eval && (a.d_out || a.status)))) {
-      const double D = log(S_W) + log(a.s_x) - 2.0 * log(S_XW);
-      if (final_eval && !isfinite(D)) flags |= FIT_STATUS_D;
-      if (a.d_trace) a.d_trace[t] = D;
-      if (final_eval && a.d_out) *a.d_out = D;
+    if (tid == 0 && final_eval && (a.d_out || a.status)) {
+      const double D = divergence_of(S_XW, S_W, a.s_x);
+      if (!isfinite(D)) flags |= FIT_STATUS_D;
+      if (a.d_out) *a.d_out = D;
     }
+    if constexpr (TRACE) {
+      if (a.d_trace && wave == 0) {
+        ring.put(t, S_XW, S_W, a.s_x, a.d_trace, lane);
+        if (final_eval && (t & 63) != 63) ring.flush(t, a.s_x, a.d_trace, lane);
+      }
+    }
+    // E_k: the four waves' sums, in wave order
+    auto slots = [&](int k, T& Eu, T& Ev) {
+      const T* src = part + (size_t)k * FIT_WAVES * 3;
+      Eu = src[1];
+      Ev = src[2];
+#pragma unroll
+      for (int w = 1; w < FIT_WAVES; ++w) {
+        Eu += src[3 * w + 1];
+        Ev += src[3 * w + 2];
+      }
+    };
     if (a.grad_w) {  // adjoint of D at this codebook (eq. (1) differentiated through the reads)
       const double gd = *a.grad_d;
       const T ca = (T)(-2.0 * gd / S_XW);
@@ -379,27 +580,29 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
 #pragma unroll
       for (int ps = 0; ps < MAXPASS; ++ps) {
         const int k = ps * FIT_NT + tid;
-        if (ps < npass && k < M) gw[k] = V2<T>{fma_t(ca, dAu[ps], cb * Eu[ps]), fma_t(ca, dAv[ps], cb * Ev[ps])};
+        if (ps < npass && k < M) {
+          T dAu, dAv, Eu, Ev;
+          cell_slope(cell[ps], fu[ps], fv[ps], dAu, dAv);
+          slots(k, Eu, Ev);
+          gw[k] = V2<T>{fma_t(ca, dAu, cb * Eu), fma_t(ca, dAv, cb * Ev)};
+        }
       }
       break;
     }
     if (final_eval) break;
 
     // ---- Jacobi update of every owned codevector ----
-    // c / s (E = E' / s), in the map type
-    T cs;
-    if constexpr (sizeof(T) == 4)
-      cs = (T)S_XW * recip((T)S_W * (T)s);
-    else
-      cs = (T)(S_XW / S_W / s);
+    const T cs = repulsion<T>(S_XW, S_W, s);
     float step = 0.0f;
 #pragma unroll
     for (int ps = 0; ps < MAXPASS; ++ps) {
       const int k = ps * FIT_NT + tid;
       if (ps < npass && k < M && Ak[ps] != (T)0) {
+        T Eu, Ev;
+        slots(k, Eu, Ev);
         const T inv = recip(Ak[ps]);
-        const T du = (gu[ps] - cs * Eu[ps]) * inv;
-        const T dv = (gv[ps] - cs * Ev[ps]) * inv;
+        const T du = (gu[ps] - cs * Eu) * inv;
+        const T dv = (gv[ps] - cs * Ev) * inv;
         if (!isfinite(du) || !isfinite(dv)) flags |= FIT_STATUS_W;
         wu[ps] += (double)du;
         wv[ps] += (double)dv;
@@ -411,7 +614,7 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
       step = wave_max_nonneg(step);
       if (lane == 0) red2[wave] = (double)step;
     }
-    __syncthreads();
+    __syncthreads();  // the new codebook; red and the slots are read
     if (a.theta >= 0.0) {
       double smax = 0.0;
 #pragma unroll
@@ -452,7 +655,7 @@ __global__ void __launch_bounds__(FIT_NT) fit_image_kernel(ImageDesc im, FitArgs
   a.write_w = fa.write_w != 0;
   a.grad_w = fa.grad_w;
   a.grad_d = fa.grad_d;
-  fit_image<T, MAXPASS>(im, a, smem);
+  fit_image<T, MAXPASS, true>(im, a, smem);
 }
 
 // Waves per SIMD the batched FP32 single-pass fit is compiled for: five
@@ -494,7 +697,7 @@ __global__ void __launch_bounds__(FIT_NT, (fit_batched_min_waves<T, MAXPASS>()))
     a.write_w = fa.write_w != 0;
     a.grad_w = fa.grad_w;
     a.grad_d = fa.grad_d ? fa.grad_d + i : nullptr;
-    fit_image<T, MAXPASS>(im, a, smem);
+    fit_image<T, MAXPASS, false>(im, a, smem);
   }
 }
 
