@@ -20,7 +20,9 @@
 //
 // A codebook of at most FIT_SMALL codevectors is one wave's work (fit_small):
 // P = 2 .. 16 lanes share a codevector and keep it, no barrier at all. A sweep is
-// a chain of latencies there: FIT_SMALL_FIGURES
+// a chain of latencies there: 0.70 us at M = 16 and 0.99 at M = 32 (with a trace;
+// FP32), against 1.85 and 1.95 on four waves with three barriers. 33 .. 64
+// codevectors would take 64 pair steps a lane, 1.4 us, against 1.6 with all else.
 //
 // The D trace needs three FP64 logarithms a sweep (0.4 us on the chain); 64
 // sweeps' sums wait in the lanes of a wave, which then takes the logarithms of
@@ -120,14 +122,13 @@ __device__ __forceinline__ void pair_blocks(const V2<T>* __restrict__ col, int n
 }
 
 // Sums over j = p, p + P, .. (steps [u0, u1) in units of four) of the
-// Gaussian terms of codevector k, then over the P lanes of each codevector.
+// Gaussian terms of codevector k: this lane's share of C, and E over the P
+// lanes of each codevector.
 template <typename T, int P>
-__device__ __forceinline__ void pair_chunk(const V2<T>* __restrict__ Wh, int k, int p, int u0, int u1, T& Cl, T& C,
-                                           T& Cu, T& Cv) {
+__device__ __forceinline__ void pair_chunk(const V2<T>* __restrict__ Wh, int k, int p, int u0, int u1, T& C, T& Cu,
+                                           T& Cv) {
   const V2<T> hk = Wh[k];
   pair_blocks<T, P>(Wh + p + u0 * 4 * P, u1 - u0, hk.u, hk.v, C, Cu, Cv);
-  Cl = C;  // this lane's share
-  C = group_sum<P>(C);
   Cu = group_sum<P>(Cu);
   Cv = group_sum<P>(Cv);
 }
@@ -161,10 +162,11 @@ __device__ __forceinline__ int pair_units(int M) {
 }
 
 // The pair phase of one sweep: wave `wave` walks its share [ua, ub) of the
-// chunk steps and writes each visited codevector's sums to
-// part[(k * 4 + wave) * 3 + 0..2]. Returns this lane's sum of its C terms.
+// chunk steps and writes each visited codevector's E to part[wave * M + k]
+// (consecutive lanes meet consecutive words). Returns this lane's sum of its C
+// terms.
 template <typename T>
-__device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, T* __restrict__ part, int M, int ua, int ub,
+__device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, V2<T>* __restrict__ part, int M, int ua, int ub,
                                              int wave, int lane) {
   double csum = 0.0;
   int cu0 = 0, k0 = 0;
@@ -176,22 +178,19 @@ __device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, T* __
     if (s0 < s1) {
       const int k = k0 + (lane >> lg), p = lane & ((1 << lg) - 1);
       const int u0 = s0 - cu0, u1 = s1 - cu0;
-      T Cl = 0, C = 0, Cu = 0, Cv = 0;
+      T C = 0, Cu = 0, Cv = 0;
       switch (lg) {
-        case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
-        default: pair_chunk<T, 64>(Wh, k, p, u0, u1, Cl, C, Cu, Cv); break;
+        case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+        default: pair_chunk<T, 64>(Wh, k, p, u0, u1, C, Cu, Cv); break;
       }
-      if (k < k0 + size) csum += (double)Cl;  // lanes past the chunk read padding and are idle
+      if (k < k0 + size) csum += (double)C;  // lanes past the chunk read padding and are idle
       if (p == 0 && k < k0 + size) {
-        T* dst = part + ((size_t)k * FIT_WAVES + wave) * 3;
-        dst[0] = C;
-        dst[1] = Cu;
-        dst[2] = Cv;
+        part[wave * M + k] = V2<T>{Cu, Cv};
       }
     }
     cu0 += nu;
@@ -354,12 +353,12 @@ __device__ void fit_small(const ImageDesc& im, const FitImageArgs& a, V2<T>* __r
   for (;; ++t) {
     const bool last = (t == im.iters) || stop;
     if (last && !need_d && !a.grad_w) break;
+    V2<T> x[NJ];  // issued first: the cell's arithmetic hides the LDS latency
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) x[i] = Wh[p + P * i];
     T fu, fv;
     cell_fetch(cell, cm, wu, wv, own, fu, fv);
     // ---- codebook terms ----
-    V2<T> x[NJ];
-#pragma unroll
-    for (int i = 0; i < NJ; ++i) x[i] = Wh[p + P * i];
     T C[2] = {}, Eu[2] = {}, Ev[2] = {};
 #pragma unroll
     for (int i = 0; i < NJ; ++i) {
@@ -370,13 +369,12 @@ __device__ void fit_small(const ImageDesc& im, const FitImageArgs& a, V2<T>* __r
       Eu[i & 1] = fma_t(e, du, Eu[i & 1]);
       Ev[i & 1] = fma_t(e, dv, Ev[i & 1]);
     }
-    const T Cl = C[0] + C[1];
-    const T Euk = group_sum<P>(Eu[0] + Eu[1]), Evk = group_sum<P>(Ev[0] + Ev[1]);
+    const T Ck = group_sum<P>(C[0] + C[1]), Euk = group_sum<P>(Eu[0] + Eu[1]), Evk = group_sum<P>(Ev[0] + Ev[1]);
     // ---- data terms, sums ----
     T A, gu, gv;
     cell_read(cell, fu, fv, A, gu, gv);
-    double S_XW = lead ? (double)A : 0.0, S_W = own ? (double)Cl : 0.0;
-    wave_sum2(S_XW, S_W);
+    double S_XW = own ? (double)A : 0.0, S_W = own ? (double)Ck : 0.0;
+    wave_sum2<P>(S_XW, S_W);
     // non-finite sums (non-finite weights or maps) end the fit at this codebook
     const bool sums_ok = isfinite(S_XW) && isfinite(S_W);  // uniform
     const bool final_eval = last || !sums_ok;
@@ -460,10 +458,9 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     __syncthreads();  // shared memory is reused by the next image
     return;
   }
-  T* part = reinterpret_cast<T*>(smem + (size_t)WL * sizeof(P2));  // [M][4 waves][3]
-  double* red = reinterpret_cast<double*>(smem + (size_t)WL * sizeof(P2) +
-                                          ((size_t)M * FIT_WAVES * 3 * sizeof(T) + 7) / 8 * 8);  // [4 waves][2]
-  double* red2 = red + 8;                                                                       // [4 waves]
+  Q2* part = Wh + WL;                                                // [4 waves][M]
+  double* red = reinterpret_cast<double*>(part + FIT_WAVES * M);     // [4 waves][2]
+  double* red2 = red + 8;                                            // [4 waves]
 
   const double s = sqrt(1.4426950408889634 / (2.0 * im.sigma * im.sigma));
   const double cu = 0.5 * im.H, cv = 0.5 * im.W;  // reference point of the LDS copy
@@ -491,7 +488,7 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     Wh[k] = h;
   }
   // slots no wave writes (a codevector's chunk may span fewer than four waves) stay 0
-  for (int i = tid; i < M * FIT_WAVES * 3; i += FIT_NT) part[i] = (T)0;
+  for (int i = tid; i < M * FIT_WAVES; i += FIT_NT) part[i] = Q2{(T)0, (T)0};
   __syncthreads();
 
   CellMaps cm;
@@ -563,13 +560,15 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     }
     // E_k: the four waves' sums, in wave order
     auto slots = [&](int k, T& Eu, T& Ev) {
-      const T* src = part + (size_t)k * FIT_WAVES * 3;
-      Eu = src[1];
-      Ev = src[2];
+      Q2 e[FIT_WAVES];
+#pragma unroll
+      for (int w = 0; w < FIT_WAVES; ++w) e[w] = part[w * M + k];
+      Eu = e[0].u;
+      Ev = e[0].v;
 #pragma unroll
       for (int w = 1; w < FIT_WAVES; ++w) {
-        Eu += src[3 * w + 1];
-        Ev += src[3 * w + 2];
+        Eu += e[w].u;
+        Ev += e[w].v;
       }
     };
     if (a.grad_w) {  // adjoint of D at this codebook (eq. (1) differentiated through the reads)
@@ -704,8 +703,7 @@ __global__ void __launch_bounds__(FIT_NT, (fit_batched_min_waves<T, MAXPASS>()))
 // Shared memory of the fit for codebooks up to m_max: the padded scaled
 // codebook, the per-wave pair sums and the reduction scratch.
 static size_t fit_smem(int m_max) {
-  return (size_t)fit_codebook_len(m_max) * sizeof(P2) + ((size_t)m_max * FIT_WAVES * 3 * sizeof(double) + 7) / 8 * 8 +
-         12 * sizeof(double) + 64;
+  return ((size_t)fit_codebook_len(m_max) + (size_t)m_max * FIT_WAVES) * sizeof(P2) + 12 * sizeof(double) + 64;
 }
 
 int fit_passes_of(int M) { return fit_passes(M); }

@@ -78,16 +78,27 @@ __device__ __forceinline__ double wave_sum(double x) {
   return lane_value(x, 63);
 }
 // Two independent wave sums in the same order as wave_sum, interleaved so
-// that each step's cross-lane moves of one overlap the other's addition.
+// that each step's cross-lane moves of one overlap the other's addition. With
+// SAME > 1 (a power of two up to 16) every aligned group of SAME lanes holds one
+// value, which counts once: the steps within the groups are left out.
+template <int SAME = 1>
 __device__ __forceinline__ void wave_sum2(double& a, double& b) {
-  a += dpp_f64<DPP_QP_1032>(a);
-  b += dpp_f64<DPP_QP_1032>(b);
-  a += dpp_f64<DPP_QP_2301>(a);
-  b += dpp_f64<DPP_QP_2301>(b);
-  a += dpp_f64<DPP_HALF_MIRROR>(a);
-  b += dpp_f64<DPP_HALF_MIRROR>(b);
-  a += dpp_f64<DPP_MIRROR>(a);
-  b += dpp_f64<DPP_MIRROR>(b);
+  if constexpr (SAME < 2) {
+    a += dpp_f64<DPP_QP_1032>(a);
+    b += dpp_f64<DPP_QP_1032>(b);
+  }
+  if constexpr (SAME < 4) {
+    a += dpp_f64<DPP_QP_2301>(a);
+    b += dpp_f64<DPP_QP_2301>(b);
+  }
+  if constexpr (SAME < 8) {
+    a += dpp_f64<DPP_HALF_MIRROR>(a);
+    b += dpp_f64<DPP_HALF_MIRROR>(b);
+  }
+  if constexpr (SAME < 16) {
+    a += dpp_f64<DPP_MIRROR>(a);
+    b += dpp_f64<DPP_MIRROR>(b);
+  }
   a += dpp_f64<DPP_BCAST15, 0xa>(a);
   b += dpp_f64<DPP_BCAST15, 0xa>(b);
   a += dpp_f64<DPP_BCAST31, 0xc>(a);
