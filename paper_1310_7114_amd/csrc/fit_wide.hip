@@ -4,14 +4,21 @@
 // One launch per sweep t = 0 .. iters + 1. Workgroup g owns the codevector
 // block g (S = 256 / P codevectors, P lanes each). Launch t first completes
 // sweep t - 1, identically in every workgroup: it adds the workgroups' FP64
-// partials of S_XW and S_W in workgroup order, forms c (and D when a trace is
-// asked for), and applies the Jacobi update to every codevector from the
-// per-codevector terms of sweep t - 1. It then reads the maps bilinearly at
-// its own codevectors of W^t, evaluates their codebook terms against the
-// whole codebook (held in LDS, centred and scaled as in the single-workgroup
-// fit so that a pair's Gaussian is exp2(-|d'|^2)), and writes the terms and
-// its partial sums for launch t + 1. Positions are FP64; positions, terms and
-// partials are double buffered by the parity of t.
+// partials of S_XW and S_W in a fixed order, forms c and applies the Jacobi
+// update to every codevector from the per-codevector terms of sweep t - 1. It
+// then reads the maps bilinearly at its own codevectors of W^t, evaluates their
+// codebook terms against the whole codebook (held in LDS, centred and scaled as
+// in the single-workgroup fit so that a pair's Gaussian is exp2(-|d'|^2)), and
+// writes the terms and its partial sums for launch t + 1. Positions are FP64;
+// positions, terms and partials are double buffered by the parity of t. When a
+// trace is asked for, one more workgroup forms D of sweep t - 1 beside the others.
+//
+// A launch is a chain of latencies, so its loads go out together (the state, the
+// partials one per lane, terms and positions of every codevector) and the map
+// corners are in flight during the pair loop. us per sweep, 2048^2, trace:
+// M = 500 4.4 (7.3 with the loads one after the other and 8 lanes per
+// codevector), M = 1000 5.7 (11.7), M = 100 3.6 (4.5); the launch and that one
+// round trip are most of the last.
 //
 // Stopping: the launch that forms W^t from W^{t-1} compares the largest step
 // with theta, and the launch after the final codebook writes w_out, the last
@@ -23,7 +30,7 @@
 #include "itc_device.h"
 
 #ifndef ITC_WIDE_LANES
-#define ITC_WIDE_LANES 8
+#define ITC_WIDE_LANES 32
 #endif
 
 namespace itc {
@@ -47,109 +54,133 @@ struct WideArgs {
   double* pos;     // [2][M][2]
   float* terms;    // [2][M][WF_TERMS]
   double* part;    // [2][G][2]: S_XW, S_W of each workgroup
-  int32_t* state;  // [0]: sweep count of the final codebook (-1: not known yet); [1]: fit done
+  int32_t* state;  // [0]: sweep count of the final codebook (-1: not known yet); [1]: launch that ended the fit, or 0
 };
 
 __host__ __device__ inline int wide_padded(int M, int P) { return (M + 4 * P - 1) / (4 * P) * (4 * P); }
 
-template <int P>
+// NP: codevectors per thread in the update of all of them, M <= NP WF_NT.
+template <int P, int NP>
 __global__ void __launch_bounds__(WF_NT) fit_wide_kernel(ImageDesc im, WideArgs a, int t) {
   static_assert(P >= 1 && P <= 64 && (P & (P - 1)) == 0, "lanes per codevector: a power of two up to 64");
   extern __shared__ __align__(16) char smem[];
   constexpr int S = WF_NT / P;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int M = a.M, G = a.G;
+  const int M = a.M, G = a.G, k0 = (int)blockIdx.x * S;
   const int Mpad = wide_padded(M, P);
-  V2<float>* Wh = reinterpret_cast<V2<float>*>(smem);                                  // [Mpad]
-  double* red = reinterpret_cast<double*>(smem + (size_t)Mpad * sizeof(V2<float>));    // [8]
-  double* wpos = red + 8;                                                              // [M][2]
+  double* red = reinterpret_cast<double*>(smem);                  // [8]
+  double2* wown = reinterpret_cast<double2*>(red + 8);            // [S]: owned positions
+  V2<float>* Wh = reinterpret_cast<V2<float>*>(wown + S);         // [Mpad]
 
   const double s = sqrt(1.4426950408889634 / (2.0 * im.sigma * im.sigma));
   const double cu = 0.5 * im.H, cv = 0.5 * im.W;
 
   // ---- complete sweep t - 1 ----
+  double2 w[NP];
   if (t == 0) {
+    if ((int)blockIdx.x == G) return;  // no sweep before this one
     if (blockIdx.x == 0 && tid == 0) {
       a.state[0] = -1;
       a.state[1] = 0;
     }
-    for (int k = tid; k < M; k += WF_NT) {
-      wpos[2 * k] = (double)a.w_init[2 * k];
-      wpos[2 * k + 1] = (double)a.w_init[2 * k + 1];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int k = i * WF_NT + tid;
+      w[i] = make_double2(0.0, 0.0);
+      if (k < M) w[i] = make_double2((double)a.w_init[2 * k], (double)a.w_init[2 * k + 1]);
     }
   } else {
-    if (a.state[1]) return;  // an earlier launch ended the fit
-    const double* pp = a.part + (size_t)((t - 1) & 1) * G * 2;
-    double sxw = 0.0, sw = 0.0;
-    for (int g = 0; g < G; ++g) {  // workgroup order, in every thread alike
-      sxw += pp[2 * g];
-      sw += pp[2 * g + 1];
+    // Everything the previous launch left is read here, in one go: the state, the workgroups' partials (one
+    // per lane), the terms and the positions. One memory latency instead of one for each.
+    const int final_t = a.state[0], done = a.state[1];
+    const double2* pp = reinterpret_cast<const double2*>(a.part) + (size_t)((t - 1) & 1) * G;
+    double2 ps = make_double2(0.0, 0.0);
+    for (int g = lane; g < G; g += 64) {
+      const double2 q = pp[g];
+      ps.x += q.x;
+      ps.y += q.y;
     }
-    if (a.d_trace && blockIdx.x == 0 && tid == 0) a.d_trace[t - 1] = log(sw) + log(*a.s_x) - 2.0 * log(sxw);
+    const double2* pprev = reinterpret_cast<const double2*>(a.pos) + (size_t)((t - 1) & 1) * M;
+    const float4* tp = reinterpret_cast<const float4*>(a.terms) + (size_t)((t - 1) & 1) * M * (WF_TERMS / 4);
+    float4 t0[NP], t1[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int k = min(i * WF_NT + tid, M - 1);
+      w[i] = pprev[k];
+      t0[i] = tp[2 * k];
+      t1[i] = tp[2 * k + 1];
+    }
+    if (done != 0 && done < t) return;  // an earlier launch ended the fit (this one may be setting it: t)
+    // fixed order, in every wave alike
+    double sxw = ps.x, sw = ps.y;
+    wave_sum2(sxw, sw);
+    if ((int)blockIdx.x == G) {  // the trace's workgroup
+      if (tid == 0) a.d_trace[t - 1] = log(sw) + log(*a.s_x) - 2.0 * log(sxw);
+      return;
+    }
     const bool sums_ok = isfinite(sxw) && isfinite(sw);
     // launch t itself may set state[0] (to t), which matters only from launch t + 1 on
-    const int final_t = a.state[0];
-    const double* pprev = a.pos + (size_t)((t - 1) & 1) * M * 2;
     if (t == a.iters + 1 || t == final_t + 1 || !sums_ok) {  // W^{t-1} is the final codebook
       if (blockIdx.x == 0) {
-        for (int k = tid; k < M; k += WF_NT) {
-          a.w_out[2 * k] = (float)pprev[2 * k];
-          a.w_out[2 * k + 1] = (float)pprev[2 * k + 1];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          const int k = i * WF_NT + tid;
+          if (k < M) {
+            a.w_out[2 * k] = (float)w[i].x;
+            a.w_out[2 * k + 1] = (float)w[i].y;
+          }
         }
         if (tid == 0) {
           if (a.iters_done) *a.iters_done = t - 1;
-          a.state[1] = 1;
+          a.state[1] = t;
         }
       }
       return;
     }
     const float cs = (float)sxw * __builtin_amdgcn_rcpf((float)sw * (float)s);  // c / s (E = E'/s)
-    const float* tp = a.terms + (size_t)((t - 1) & 1) * M * WF_TERMS;
     float step = 0.0f;
-    for (int k = tid; k < M; k += WF_NT) {
-      double u = pprev[2 * k], v = pprev[2 * k + 1];
-      const float A = tp[WF_TERMS * k];
-      if (A != 0.0f) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const float A = t0[i].x;
+      if (i * WF_NT + tid < M && A != 0.0f) {
         const float inv = __builtin_amdgcn_rcpf(A);
-        const float du = (tp[WF_TERMS * k + 1] - cs * tp[WF_TERMS * k + 3]) * inv;
-        const float dv = (tp[WF_TERMS * k + 2] - cs * tp[WF_TERMS * k + 4]) * inv;
-        u += (double)du;
-        v += (double)dv;
+        const float du = (t0[i].y - cs * t0[i].w) * inv;
+        const float dv = (t0[i].z - cs * t1[i].x) * inv;
+        w[i].x += (double)du;
+        w[i].y += (double)dv;
         step = fmaxf(step, (float)sqrt((double)du * du + (double)dv * dv));
       }
-      wpos[2 * k] = u;
-      wpos[2 * k + 1] = v;
     }
     if (a.theta >= 0.0) {  // uniform
       step = wave_max_nonneg(step);
       if (lane == 0) red[wave] = (double)step;
       __syncthreads();
       double smax = 0.0;
-      for (int w = 0; w < WF_NT / 64; ++w) smax = fmax(smax, red[w]);
+      for (int q = 0; q < WF_NT / 64; ++q) smax = fmax(smax, red[q]);
       if (smax <= a.theta && blockIdx.x == 0 && tid == 0) a.state[0] = t;  // W^t is final
+      __syncthreads();  // red is written again below
     }
   }
-  __syncthreads();
 
   // ---- W^t: the owned positions to the work buffer, every position to LDS ----
-  double* pcur = a.pos + (size_t)(t & 1) * M * 2;
-  for (int k = tid; k < Mpad; k += WF_NT) {
-    V2<float> h{(float)WF_FAR, (float)WF_FAR};  // padding: Gaussian exactly 0
+  double2* pcur = reinterpret_cast<double2*>(a.pos) + (size_t)(t & 1) * M;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int k = i * WF_NT + tid;
     if (k < M) {
-      const double u = wpos[2 * k], v = wpos[2 * k + 1];
-      h = V2<float>{(float)(s * (u - cu)), (float)(s * (v - cv))};
-      if (k / S == (int)blockIdx.x) {
-        pcur[2 * k] = u;
-        pcur[2 * k + 1] = v;
+      Wh[k] = V2<float>{(float)(s * (w[i].x - cu)), (float)(s * (w[i].y - cv))};
+      if (k >= k0 && k < k0 + S) {
+        pcur[k] = w[i];
+        wown[k - k0] = w[i];
       }
     }
-    Wh[k] = h;
   }
+  for (int k = M + tid; k < Mpad; k += WF_NT) Wh[k] = V2<float>{(float)WF_FAR, (float)WF_FAR};  // Gaussian exactly 0
   __syncthreads();
 
   // ---- terms of the owned codevectors ----
   const int slot = tid / P, p = tid % P;
-  const int k = (int)blockIdx.x * S + slot;
+  const int k = k0 + slot;
   const bool own = k < M;
   const int H = im.H, W = im.W;
   const uint32_t planeb = (uint32_t)(im.plane * (int64_t)sizeof(float));
@@ -157,7 +188,7 @@ __global__ void __launch_bounds__(WF_NT) fit_wide_kernel(ImageDesc im, WideArgs 
   float av[4] = {0.f, 0.f, 0.f, 0.f}, mu[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {0.f, 0.f, 0.f, 0.f};
   float fu = 0.f, fv = 0.f, C = 0.f, Cu = 0.f, Cv = 0.f;
   if (own) {
-    const double uk = wpos[2 * k], vk = wpos[2 * k + 1];
+    const double uk = wown[slot].x, vk = wown[slot].y;
     // bilinear corners of the cell holding w_k; off-lattice corners read 0
     const bool inside = uk > -1.0 && uk < (double)H && vk > -1.0 && vk < (double)W;
     const double fu0 = inside ? floor(uk) : 0.0, fv0 = inside ? floor(vk) : 0.0;
@@ -212,41 +243,36 @@ __global__ void __launch_bounds__(WF_NT) fit_wide_kernel(ImageDesc im, WideArgs 
     Gu = __builtin_fmaf(b, __builtin_fmaf((float)di - fu, av[c], -mu[c]), Gu);
     Gv = __builtin_fmaf(b, __builtin_fmaf((float)dj - fv, av[c], -mv[c]), Gv);
   }
-  const bool writer = own && p == 0;
-  if (writer) {
-    float* tc = a.terms + (size_t)(t & 1) * M * WF_TERMS + (size_t)WF_TERMS * k;
-    tc[0] = A;
-    tc[1] = Gu;
-    tc[2] = Gv;
-    tc[3] = Cu;
-    tc[4] = Cv;
-    tc[5] = C;
+  if (own && p == 0) {
+    float4* tc = reinterpret_cast<float4*>(a.terms) + ((size_t)(t & 1) * M + k) * (WF_TERMS / 4);
+    tc[0] = make_float4(A, Gu, Gv, Cu);
+    tc[1] = make_float4(Cv, C, 0.f, 0.f);
   }
-  // ---- the workgroup's partials of S_XW and S_W: FP64, fixed order ----
-  double sxw = wave_sum(writer ? (double)A : 0.0);
-  double sw = wave_sum(writer ? (double)C : 0.0);
-  if (lane == 0) {  // red[] was last read before the barrier above
+  // ---- the workgroup's partials of S_XW and S_W: FP64, fixed order (the P lanes of a codevector hold one
+  // value; at most 16 of them give it) ----
+  constexpr int SAME = P < 16 ? P : 16;
+  double sxw = own && p < SAME ? (double)A : 0.0, sw = own && p < SAME ? (double)C : 0.0;
+  wave_sum2<SAME>(sxw, sw);
+  if (lane == 0) {
     red[2 * wave] = sxw;
     red[2 * wave + 1] = sw;
   }
   __syncthreads();
   if (tid == 0) {
     double tx = 0.0, tw = 0.0;
-    for (int w = 0; w < WF_NT / 64; ++w) {
-      tx += red[2 * w];
-      tw += red[2 * w + 1];
+    for (int q = 0; q < WF_NT / 64; ++q) {
+      tx += red[2 * q];
+      tw += red[2 * q + 1];
     }
-    double* pc = a.part + (size_t)(t & 1) * G * 2;
-    pc[2 * blockIdx.x] = tx;
-    pc[2 * blockIdx.x + 1] = tw;
+    reinterpret_cast<double2*>(a.part)[(size_t)(t & 1) * G + blockIdx.x] = make_double2(tx, tw);
   }
 }
 
 }  // namespace
 
 // Lanes per codevector: a pair loop of M / P steps per lane against more
-// workgroups, each with the per-launch fixed cost (the update of all M
-// codevectors). 8 measured fastest for M = 100 and M = 500 among 4 .. 64.
+// workgroups, each with the update of all M codevectors. us per sweep at P = 8,
+// 16, 32, 64: M = 500 5.6, 4.7, 4.4, 4.7; M = 100 4.1, 3.8, 3.6, 3.8.
 constexpr int WF_P = ITC_WIDE_LANES;
 
 int fit_wide_groups(int M) { return (M + WF_NT / WF_P - 1) / (WF_NT / WF_P); }
@@ -264,7 +290,7 @@ size_t fit_wide_work_bytes(int M) {
 
 size_t fit_wide_smem(int M) {
   return (size_t)wide_padded(M, WF_P) * sizeof(V2<float>) + 8 * sizeof(double) +
-         (size_t)M * 2 * sizeof(double);
+         (size_t)(WF_NT / WF_P) * sizeof(double2);
 }
 
 hipError_t launch_fit_wide(const ImageDesc& im, const void* maps, const double* s_x, const float* w_init, int iters,
@@ -288,9 +314,14 @@ hipError_t launch_fit_wide(const ImageDesc& im, const void* maps, const double* 
   a.part = (double*)(w + wide_pos_bytes(M) + wide_terms_bytes(M));
   a.state = (int32_t*)(w + wide_pos_bytes(M) + wide_terms_bytes(M) + wide_part_bytes(M));
   const size_t smem = fit_wide_smem(M);
-  const dim3 grid(a.G), block(WF_NT);
+  const dim3 grid(a.G + (d_trace ? 1 : 0)), block(WF_NT);
   for (int t = 0; t <= iters + 1; ++t) {
-    hipLaunchKernelGGL(fit_wide_kernel<WF_P>, grid, block, smem, s, im, a, t);
+    if (M <= WF_NT)
+      hipLaunchKernelGGL((fit_wide_kernel<WF_P, 1>), grid, block, smem, s, im, a, t);
+    else if (M <= 2 * WF_NT)
+      hipLaunchKernelGGL((fit_wide_kernel<WF_P, 2>), grid, block, smem, s, im, a, t);
+    else
+      hipLaunchKernelGGL((fit_wide_kernel<WF_P, 4>), grid, block, smem, s, im, a, t);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
