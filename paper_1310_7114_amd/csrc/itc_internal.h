@@ -174,10 +174,12 @@ struct LiteralArgs {
   int32_t iters;
   int32_t nvx;      // row blocks of the V(X) sum
   double omega, theta;
-  double* taps;     // [R + 1] g, then [2R + 1] window overlaps
+  double* taps;     // [R + 1] g
+  double* tabs;     // [12 R + 8] overlap tables
   double* vx_part;  // [nvx]
-  double* terms;    // [6 M]: a, b_u, b_v, e, d_u, d_v
-  int32_t* state;
+  double* terms[2];  // [6 M] each: a, b_u, b_v, e, d_u, d_v per codevector, by the parity of the sweep
+  int2* pos;         // [2][M] lattice points, by the parity of the sweep
+  int32_t* state;    // [2]: sweep count of the final codebook (-1: not known), launch that ended the fit (0: none)
   double* d_trace;      // [iters + 1] or null
   int32_t* iters_done;  // or null
 };

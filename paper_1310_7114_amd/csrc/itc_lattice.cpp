@@ -803,10 +803,12 @@ itc_status itc_lattice_fit_batched(itc_plan* p, const void* maps, const void* w_
 }
 
 // Algorithm 1: the work buffer holds the maps of P (unless the caller gives
-// P), then the taps and window overlaps, the V(X) row-block sums, the
-// per-codevector sums and the state.
+// P), then the taps, the V(X) row-block sums, the per-codevector sums and the
+// state. The second sums, the overlap tables and the positions lie over the
+// moment planes of the maps, which the loop does not read, where these are
+// large enough, and behind the state otherwise.
 struct LiteralLayout {
-  size_t maps, taps, vx, terms, state, total;
+  size_t maps, taps, vx, terms, state, second, total;
   int R, nvx;
 };
 
@@ -824,6 +826,14 @@ static bool literal_layout(const itc_lattice_desc& d, int32_t M, double omega, i
   L.terms = L.vx + (size_t)L.nvx * sizeof(double);
   L.state = L.terms + (size_t)6 * M * sizeof(double);
   L.total = (L.state + 8 + 255) / 256 * 256;
+  const size_t second = ((size_t)6 * M + 12 * R + 8) * sizeof(double) + (size_t)2 * M * sizeof(int2);
+  const size_t plane = (size_t)itc::plane_elems_of(d.height, d.width) * sizeof(float);
+  if (with_maps && second <= 2 * plane) {
+    L.second = L.maps + plane;
+  } else {
+    L.second = L.total;
+    L.total += (second + 255) / 256 * 256;
+  }
   return true;
 }
 
@@ -895,7 +905,10 @@ static itc_status literal_fit_impl(const itc_lattice_desc* d, const void* weight
   la.theta = theta;
   la.taps = reinterpret_cast<double*>(wb + L.taps);
   la.vx_part = reinterpret_cast<double*>(wb + L.vx);
-  la.terms = reinterpret_cast<double*>(wb + L.terms);
+  la.terms[0] = reinterpret_cast<double*>(wb + L.terms);
+  la.terms[1] = reinterpret_cast<double*>(wb + L.second);
+  la.tabs = la.terms[1] + (size_t)6 * M;
+  la.pos = reinterpret_cast<int2*>(la.tabs + 12 * L.R + 8);
   la.state = reinterpret_cast<int32_t*>(wb + L.state);
   la.d_trace = d_trace;
   la.iters_done = iters_done;
