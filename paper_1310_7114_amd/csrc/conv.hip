@@ -1,4 +1,4 @@
-// Separable Gaussian convolution maps of a lattice weight image (Section 3.1:
+// FP64 separable Gaussian convolution maps of a lattice weight image (Section 3.1:
 // the Parzen sum of delta impulses is the image convolved with a Gaussian; for
 // small widths the 2-D mask factorises into 1-D masks). One pass produces
 //   A   = (I *_v g) *_u g,   M_u = (I *_v g) *_u tg,   M_v = (I *_v tg) *_u g
@@ -23,9 +23,8 @@
 //      the maps' panel layout; h*A is summed per lane in FP64 and per wave
 //      into the S_X partial of each SX_ROWS-row group.
 // Four waves per workgroup share one ring: at the LDS budget of one ring the
-// chip holds twice the waves of a two-wave workgroup (the FP32 convolution of
-// 64 x 1024^2 images took 0.47 ms against 0.56 ms with two), so one wave's
-// LDS, scalar and memory instructions issue beside the others' FMAs. Taps
+// chip holds twice the waves of a two-wave workgroup, so one wave's LDS, scalar
+// and memory instructions issue beside the others' FMAs. Taps
 // are computed once per segment in FP64 (one lane per tap) and held in scalar
 // registers; tap loops are unrolled for the class.
 #include "itc_device.h"
@@ -41,7 +40,9 @@ namespace itc {
 constexpr int CONV_AHEAD = ITC_CONV_AHEAD;
 static_assert(CONV_AHEAD >= 1 && CONV_AHEAD * 6 * CONV_KB <= 63, "pending memory operations within the counter");
 
-template <typename T, int R>
+using T = double;  // the maps' real type
+
+template <int R>
 struct ConvGeom {
   static constexpr int CH = CONV_CH;
   static constexpr int J0 = (2 * R + CH - 1) / CH;  // chunks before the first column pass
@@ -56,42 +57,28 @@ struct ConvGeom {
   static_assert(XW <= 2 * CONV_TW, "two staged columns per lane");
 };
 
-// Raw stored weight at element offset `i`, kept unconverted until staging so
-// that the global load's latency hides behind a whole chunk of arithmetic.
-// FP32 kernels keep 32 bits (u8 value or f32 bits; FP64 weights are narrowed
-// to f32 at load), FP64 kernels keep 64 bits.
-template <typename T>
-struct RawOf {
-  using type = uint32_t;
-};
-template <>
-struct RawOf<double> {
-  using type = uint64_t;
-};
-
-// Load of a stored weight of type WT kept as raw bits (FP64 weights are
-// narrowed to f32 in FP32 kernels), and its conversion to the real type.
-template <typename T, typename WT>
-__device__ __forceinline__ typename RawOf<T>::type load_raw(rsrc_t r, uint32_t voff, uint32_t soff) {
-  using U = typename RawOf<T>::type;
+// Raw stored weight (u8 value, f32 or f64 bits), kept unconverted until
+// staging so that the global load's latency hides behind a whole chunk of
+// arithmetic, and its conversion.
+using Raw = uint64_t;
+template <typename WT>
+__device__ __forceinline__ Raw load_raw(rsrc_t r, uint32_t voff, uint32_t soff) {
   const WT v = buf_load<WT>(r, voff, soff);
   if constexpr (sizeof(WT) == 1)
-    return (U)v;
+    return (Raw)v;
   else if constexpr (sizeof(WT) == 4)
-    return (U)__builtin_bit_cast(uint32_t, v);
-  else if constexpr (sizeof(U) == 8)
+    return (Raw)__builtin_bit_cast(uint32_t, v);
+  else
     return __builtin_bit_cast(uint64_t, v);
-  else
-    return __builtin_bit_cast(uint32_t, (float)v);
 }
-template <typename T, typename WT>
-__device__ __forceinline__ T raw_value(typename RawOf<T>::type r) {
+template <typename WT>
+__device__ __forceinline__ double raw_value(Raw r) {
   if constexpr (sizeof(WT) == 1)
-    return (T)(uint32_t)r;
-  else if constexpr (sizeof(WT) == 4 || sizeof(r) == 4)
-    return (T)__builtin_bit_cast(float, (uint32_t)r);
+    return (double)(uint32_t)r;
+  else if constexpr (sizeof(WT) == 4)
+    return (double)__builtin_bit_cast(float, (uint32_t)r);
   else
-    return (T)__builtin_bit_cast(double, (uint64_t)r);
+    return __builtin_bit_cast(double, r);
 }
 
 // Calls f(WT{}) with WT the stored weight type: one uniform branch per call.
@@ -107,11 +94,11 @@ __device__ __forceinline__ void with_weight_type(int wdtype, F&& f) {
 
 // Column pass of one wave: rows KB w .. KB w + KB - 1 of the chunk whose window starts at
 // ring block `jb` (chunk index minus J0).
-template <typename T, int R, int WV>
+template <int R, int WV>
 __device__ __forceinline__ void column_pass(const T* __restrict__ ring0, const T* __restrict__ ring1, int jb,
                                             int lane, const T (&g)[R + 1], const T (&tg)[R + 1],
                                             T (&a)[CONV_KB], T (&mu)[CONV_KB], T (&mv)[CONV_KB]) {
-  using G = ConvGeom<T, R>;
+  using G = ConvGeom<R>;
   constexpr int KB = CONV_KB;
   constexpr int NBLK = (WV * KB + G::NWIN + CONV_CH - 1) / CONV_CH;  // blocks touched
 #pragma unroll
@@ -143,13 +130,12 @@ __device__ __forceinline__ void column_pass(const T* __restrict__ ring0, const T
   }
 }
 
-template <typename T, int R, typename WT>
+template <int R, typename WT>
 __device__ __forceinline__ void conv_segment_t(const ImageDesc& im, int strip, int s0, int S,
                                              const char* __restrict__ wbase, char* __restrict__ mbase,
                                              char* __restrict__ smem) {
-  using G = ConvGeom<T, R>;
+  using G = ConvGeom<R>;
   constexpr int CH = CONV_CH, KB = CONV_KB;
-  using Raw = typename RawOf<T>::type;
   T* ring0 = reinterpret_cast<T*>(smem);
   T* ring1 = ring0 + G::RING_ELEMS;
   T* xin = ring1 + G::RING_ELEMS;
@@ -224,9 +210,9 @@ __device__ __forceinline__ void conv_segment_t(const ImageDesc& im, int strip, i
         const uint32_t oout = (uint32_t)(o < s0 || o >= seg_end) << 31;   // uniform
         const uint32_t yb = (yout ? 0u : (uint32_t)y * rowbytes) | yout;
         const uint32_t ob = (oout ? 0u : (uint32_t)o * rowbytes) | oout;
-        raw0[p][r] = load_raw<T, WT>(wres, (yb + c0 * es) | bad0, 0);
-        raw1[p][r] = load_raw<T, WT>(wres, (yb + c1 * es) | bad1, 0);
-        hraw[p][r] = load_raw<T, WT>(wres, (ob + cc * es) | badc, 0);
+        raw0[p][r] = load_raw<WT>(wres, (yb + c0 * es) | bad0, 0);
+        raw1[p][r] = load_raw<WT>(wres, (yb + c1 * es) | bad1, 0);
+        hraw[p][r] = load_raw<WT>(wres, (ob + cc * es) | badc, 0);
       }
     }
   };
@@ -238,9 +224,9 @@ __device__ __forceinline__ void conv_segment_t(const ImageDesc& im, int strip, i
     T* x = xin + wave * KB * G::XP + lane;
 #pragma unroll
     for (int r = 0; r < KB; ++r) {
-      x[r * G::XP] = raw_value<T, WT>(raw0[p][r]) * scale;
-      x[r * G::XP + CONV_TW] = raw_value<T, WT>(raw1[p][r]) * scale;
-      hv[r] = raw_value<T, WT>(hraw[p][r]);
+      x[r * G::XP] = raw_value<WT>(raw0[p][r]) * scale;
+      x[r * G::XP + CONV_TW] = raw_value<WT>(raw1[p][r]) * scale;
+      hv[r] = raw_value<WT>(hraw[p][r]);
     }
   };
   // as many (dropped) stores as a column pass makes: the prologue and the
@@ -310,13 +296,13 @@ __device__ __forceinline__ void conv_segment_t(const ImageDesc& im, int strip, i
     const int o0 = s0 + (j - G::J0) * CH + wave * KB;
     T a[KB], mu[KB], mv[KB];
     switch (wave) {  // uniform; the window offset of each wave is compile-time
-      case 0: column_pass<T, R, 0>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv); break;
-      case 1: column_pass<T, R, 1>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv); break;
+      case 0: column_pass<R, 0>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv); break;
+      case 1: column_pass<R, 1>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv); break;
       case 2:
-        if constexpr (CONV_WAVES > 2) column_pass<T, R, 2>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv);
+        if constexpr (CONV_WAVES > 2) column_pass<R, 2>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv);
         break;
       default:
-        if constexpr (CONV_WAVES > 3) column_pass<T, R, 3>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv);
+        if constexpr (CONV_WAVES > 3) column_pass<R, 3>(ring0, ring1, j - G::J0, lane, g, tg, a, mu, mv);
         break;
     }
     // columns past the width inside the last panel are stored too (never
@@ -362,44 +348,23 @@ __device__ __forceinline__ void conv_segment_t(const ImageDesc& im, int strip, i
 
 // One segment for the image's stored weight type (one uniform branch per
 // segment, so the loop carries no type switch).
-template <typename T, int R>
+template <int R>
 __device__ __forceinline__ void conv_segment(const ImageDesc& im, int strip, int s0, int S,
                                              const char* __restrict__ wbase, char* __restrict__ mbase,
                                              char* __restrict__ smem) {
-  with_weight_type(im.wdtype, [&](auto wt) { conv_segment_t<T, R, decltype(wt)>(im, strip, s0, S, wbase, mbase, smem); });
+  with_weight_type(im.wdtype, [&](auto wt) { conv_segment_t<R, decltype(wt)>(im, strip, s0, S, wbase, mbase, smem); });
 }
 
 // ---------------------------------------------------------------------------
 // single image: one workgroup per (strip, segment); exact LDS for the class
 // ---------------------------------------------------------------------------
-template <typename T, int R>
+template <int R>
 __global__ void __launch_bounds__(CONV_NT) conv_image_kernel(ImageDesc im, int S, const char* wbase,
                                                              char* mbase) {
-  __shared__ __align__(16) char smem[ConvGeom<T, R>::SMEM];
+  __shared__ __align__(16) char smem[ConvGeom<R>::SMEM];
   const int strip = blockIdx.x % im.nstrips;
   const int seg = blockIdx.x / im.nstrips;
-  conv_segment<T, R>(im, strip, seg * S, S, wbase, mbase, smem);
-}
-
-// ---------------------------------------------------------------------------
-// batched: persistent workgroups of one radius class walk its tile list
-// (cost-sorted by the planner, split into one sublist per XCD: block b walks
-// sublist b mod CONV_XCDS, so the strips of a segment row, whose input
-// windows overlap, read those lines through one L2)
-// ---------------------------------------------------------------------------
-template <typename T, int R>
-__global__ void __launch_bounds__(CONV_NT) conv_tiles_kernel(const ImageDesc* __restrict__ images,
-                                                             const ConvTile* __restrict__ tiles, XcdSplit xs,
-                                                             const char* wbase, char* mbase) {
-  __shared__ __align__(16) char smem[ConvGeom<T, R>::SMEM];
-  const int x = blockIdx.x % CONV_XCDS, nx = gridDim.x / CONV_XCDS;
-  const int end = xs.beg[x + 1];
-  for (int i = xs.beg[x] + (int)blockIdx.x / CONV_XCDS; i < end; i += nx) {
-    const ConvTile t = tiles[i];
-    const ImageDesc im = images[t.img];
-    conv_segment<T, R>(im, t.strip, t.s0, t.S, wbase, mbase, smem);
-    __syncthreads();  // the next tile reuses the shared memory
-  }
+  conv_segment<R>(im, strip, seg * S, S, wbase, mbase, smem);
 }
 
 // S_X = the sum of an image's FP64 partials, in a fixed order that depends
@@ -414,7 +379,6 @@ __global__ void __launch_bounds__(256) sx_total_kernel(ImageDesc im, const char*
 // ---------------------------------------------------------------------------
 // host-side launch helpers
 // ---------------------------------------------------------------------------
-#define ITC_FOR_CLASSES_F32(X) X(2) X(3) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(24) X(28) X(32)
 #define ITC_FOR_CLASSES_F64(X) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(20) X(24)
 
 // Segment length for a single image: enough workgroups to fill the chip,
@@ -431,70 +395,18 @@ int conv_segment_rows(const ImageDesc& im) {
 }
 
 hipError_t launch_conv_image(bool f64, const ImageDesc& im, const void* w, void* m, hipStream_t s) {
-  if (conv_uses_mx(f64, im.wdtype, w, im.weight_off, im.pitch)) return launch_conv_mx_image(im, w, m, s);
+  if (!f64)
+    return conv_uses_mx(f64, im.wdtype, w, im.weight_off, im.pitch) ? launch_conv_mx_image(im, w, m, s)
+                                                                    : launch_conv_f32_image(im, w, m, s);
   const int S = conv_segment_rows(im);
   const dim3 grid(im.nstrips * ((im.H + S - 1) / S));
-#define ITC_CASE_F(RR)                                                                           \
+#define ITC_CASE(RR)                                                                            \
   case RR:                                                                                      \
-    hipLaunchKernelGGL((conv_image_kernel<float, RR>), grid, dim3(CONV_NT), 0, s, im, S,         \
-                       (const char*)w, (char*)m);                                                \
+    hipLaunchKernelGGL((conv_image_kernel<RR>), grid, dim3(CONV_NT), 0, s, im, S, (const char*)w, \
+                       (char*)m);                                                               \
     return hipGetLastError();
-#define ITC_CASE_D(RR)                                                                           \
-  case RR:                                                                                      \
-    hipLaunchKernelGGL((conv_image_kernel<double, RR>), grid, dim3(CONV_NT), 0, s, im, S,        \
-                       (const char*)w, (char*)m);                                                \
-    return hipGetLastError();
-  if (f64) {
-    switch (im.rclass) { ITC_FOR_CLASSES_F64(ITC_CASE_D) default: return hipErrorInvalidValue; }
-  }
-  switch (im.rclass) { ITC_FOR_CLASSES_F32(ITC_CASE_F) default: return hipErrorInvalidValue; }
-#undef ITC_CASE_F
-#undef ITC_CASE_D
-}
-
-hipError_t launch_conv_tiles(bool f64, int rclass, const ImageDesc* d_images, const ConvTile* d_tiles,
-                             const XcdSplit& xs, const void* w, void* m, int grid, hipStream_t s) {
-  if (rclass >= CONV_MX_CLASS) return hipErrorInvalidValue;  // launched by launch_conv_mx_tiles
-  if (grid % CONV_XCDS != 0) return hipErrorInvalidValue;
-#define ITC_CASE_F(RR)                                                                              \
-  case RR:                                                                                         \
-    hipLaunchKernelGGL((conv_tiles_kernel<float, RR>), dim3(grid), dim3(CONV_NT), 0, s, d_images,    \
-                       d_tiles, xs, (const char*)w, (char*)m);                                      \
-    return hipGetLastError();
-#define ITC_CASE_D(RR)                                                                              \
-  case RR:                                                                                         \
-    hipLaunchKernelGGL((conv_tiles_kernel<double, RR>), dim3(grid), dim3(CONV_NT), 0, s, d_images,   \
-                       d_tiles, xs, (const char*)w, (char*)m);                                      \
-    return hipGetLastError();
-  if (f64) {
-    switch (rclass) { ITC_FOR_CLASSES_F64(ITC_CASE_D) default: return hipErrorInvalidValue; }
-  }
-  switch (rclass) { ITC_FOR_CLASSES_F32(ITC_CASE_F) default: return hipErrorInvalidValue; }
-#undef ITC_CASE_F
-#undef ITC_CASE_D
-}
-
-int conv_tiles_blocks_per_cu(bool f64, int rclass) {
-  if (rclass >= CONV_MX_CLASS) return conv_mx_blocks_per_cu(rclass - CONV_MX_CLASS);
-  int nb = 0;
-#define ITC_CASE_F(RR)                                                                               \
-  case RR:                                                                                          \
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, conv_tiles_kernel<float, RR>, CONV_NT, 0) != \
-        hipSuccess)                                                                                 \
-      return 0;                                                                                     \
-    return nb;
-#define ITC_CASE_D(RR)                                                                                \
-  case RR:                                                                                           \
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, conv_tiles_kernel<double, RR>, CONV_NT, 0) != \
-        hipSuccess)                                                                                  \
-      return 0;                                                                                      \
-    return nb;
-  if (f64) {
-    switch (rclass) { ITC_FOR_CLASSES_F64(ITC_CASE_D) default: return 0; }
-  }
-  switch (rclass) { ITC_FOR_CLASSES_F32(ITC_CASE_F) default: return 0; }
-#undef ITC_CASE_F
-#undef ITC_CASE_D
+  switch (im.rclass) { ITC_FOR_CLASSES_F64(ITC_CASE) default: return hipErrorInvalidValue; }
+#undef ITC_CASE
 }
 
 hipError_t launch_sx_finalize(const ImageDesc& img, const void* maps, double* s_x, hipStream_t s) {

@@ -1,0 +1,445 @@
+// FP32 convolution maps (A, M_u, M_v and the FP64 partials of S_X, as in
+// conv.hip) on the FP32 matrix cores, for what the split-FP16 kernel does not
+// take: FP32 and FP64 weights, and 8-bit rows that are not 4-byte aligned.
+//
+// Each 1-D pass is a banded Toeplitz product: sixteen outputs along an axis are
+// a 16 x K window of inputs times the K x 16 matrix T[k][n] = f(n + RA - k), RA the
+// radius rounded up to 4, K = 16 + 2 RA, f zero past the true radius, evaluated
+// with v_mfma_f32_16x16x4_f32: FP32 operands, products and sums, as in a direct
+// FP32 sum (largest error against 64 bits over R = 1..24: 5.0e-7 of the largest
+// map value, 5.3e-7 as vector FMAs). The matrix unit runs at twice the rate of
+// unpacked vector FMAs, so the band's zeros (K = 40 terms instead of 25 at R = 12)
+// still leave it ahead, and the vector unit only stages and addresses.
+//
+// Work decomposition: a workgroup of four waves owns a strip of 64 columns and a
+// segment of rows (starting at a multiple of SX_ROWS) and streams down it in
+// chunks of 16 rows. Per chunk:
+//   1. staging: the chunk's 16 input rows with their column halo, fetched a chunk
+//      earlier (16 bytes per lane and load where no group of four straddles the
+//      width), scaled, into one of two LDS buffers; one barrier;
+//   2. row pass: wave w makes columns 16w..16w+15 of R0 and R1 and writes them to
+//      its ring, column-major; no other wave reads them;
+//   3. column pass, 2 RA rows behind: ring columns are the A operand, so a lane
+//      holds four adjacent columns of one output row: one 16-byte store per map,
+//      a 16 x 16 tile of a panel is one contiguous KiB. h A goes into an FP64
+//      partial of S_X per SX_ROWS-row group; h is loaded again (from L2).
+// The k index of a product is permuted so that a lane's operands of four steps
+// (two in the last group of eight) are consecutive in LDS: one 16-byte read.
+// Pitches of 4 x odd words spread 16 lanes' reads over all banks.
+//
+// A zero tap times a non-finite value is not zero. Every output of a 16 x 16 tile
+// sees every value of its window, so such a value (a weight that is not finite, an
+// overflow) leaves none of the tile's A or M_v finite; a wave that finds one
+// computes its columns of the segment again from the window sums, so that the
+// value reaches exactly the pixels within R of it. The test rides on the S_X
+// sum: as eight multiply-adds per row pass and a vote of the workgroup it took
+// 60 us of 280 (R = 4, below).
+//
+// Bound by memory (4 B read and 12 B written per pixel) up to R of about 8, then
+// by the matrix unit. 64 x 1024^2 FP32 weights: R = 4 209 us (5.1 TB/s; 290 us
+// with vector FMAs), R = 12 275 us (362), R = 24 380 us (600); one 1024^2
+// image: 10.4 us (12.4), 12.4 us (16.4), 21 us (33). One to three chunks of
+// loads in flight are the same; stores past the caches take 211 us at R = 4, as
+// ordinary stores 242.
+#include <type_traits>
+#include <utility>
+
+#include "itc_device.h"
+
+namespace itc {
+
+namespace {
+
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
+
+constexpr int CF_NT = 256, CF_CH = 16;
+static_assert(SX_SLOTS == CF_NT / 64 && CONV_TW == 4 * MAP_PANEL, "one S_X slot and one panel per wave");
+constexpr int CF_STREAM = 2;  // map stores are non-temporal
+
+template <int RA>
+struct CfGeom {
+  static_assert(RA % 4 == 0 && RA >= 4 && RA <= 32, "aligned radius");
+  static constexpr int K = 16 + 2 * RA, KS = K / 4;          // window, MFMA steps
+  static constexpr int NG = K / 16, REM = K % 16;            // groups of 16, and 8 or none
+  static constexpr int J0 = (2 * RA + CF_CH - 1) / CF_CH;  // chunks before the first column pass
+  static constexpr int NB = J0 + 1;                          // ring blocks of 16 rows
+  static constexpr int RINGP = NB * CF_CH + 4;               // ring column pitch
+  static constexpr int SW = 48 + K;                          // staged columns (image columns v0 - RA + c)
+  static constexpr int SWP = SW + 4;
+  // a chunk, and a slot per spare item of the threads' equal shares of groups of four
+  static constexpr int STAGE = CF_CH * SWP + 4 * ((4 * SW + CF_NT - 1) / CF_NT * CF_NT - 4 * SW);
+  static constexpr int RING = CONV_TW * RINGP;
+  static constexpr int WGS = RA <= 24 ? 3 : 2;               // workgroups per compute unit: LDS allows no more
+  static constexpr size_t SMEM = (2 * (size_t)STAGE + 2 * (size_t)RING) * sizeof(float);
+  static_assert(RINGP / 4 % 2 == 1 && SWP / 4 % 2 == 1, "bank-spread pitches");
+  static_assert(16 * RINGP >= 128, "a wave's ring holds the taps");
+  static_assert(REM == 0 || REM == 8, "K is a multiple of eight");
+};
+
+__device__ __forceinline__ f4_t mfma(float a, float b, f4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Tap f(t) for the k of step st held by lane group q, f symmetric or odd.
+template <int RA>
+__device__ __forceinline__ constexpr int k_of(int st, int q) {
+  using G = CfGeom<RA>;
+  return st < 4 * G::NG ? 16 * (st / 4) + 4 * q + st % 4 : 16 * G::NG + 2 * q + (st - 4 * G::NG);
+}
+
+// A wave's 16 columns of the segment from the window sums themselves, for
+// segments with non-finite values: every pixel sums its rows with g and tg,
+// then over the rows; t = 0 has no tg term. `taps` is LDS of this wave.
+template <typename WT>
+__device__ __forceinline__ void segment_by_windows(const ImageDesc& im, int strip, int s0, int seg_end,
+                                                   const char* wbase, char* mbase, float* taps) {
+  const int H = im.H, W = im.W, R = im.R;
+  const WT* x = reinterpret_cast<const WT*>(wbase + im.weight_off);
+  float* maps = reinterpret_cast<float*>(mbase + im.map_off);
+  const float scale = (float)im.scale;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = tid >> 6;
+  if (lane <= R) {
+    const double gl = exp(-0.5 / (im.sigma * im.sigma) * (double)(lane * lane));
+    taps[lane] = (float)gl;
+    taps[64 + lane] = (float)((double)lane * gl);
+  }
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  const int v = strip * CONV_TW + 16 * wave + (lane & 15);
+  double* part = reinterpret_cast<double*>(mbase + im.map_off + im.part_off) + (int64_t)strip * im.nsxg * SX_SLOTS + wave;
+  double sxd = 0.0;
+#pragma unroll 1
+  for (int o0 = s0; o0 < seg_end; o0 += 4) {
+    const int o = o0 + (lane >> 4);
+    if (o < seg_end && v < im.npanels * MAP_PANEL) {
+      float a = 0.f, mu = 0.f, mv = 0.f;
+#pragma unroll 1
+      for (int y = max(o - R, 0); y <= min(o + R, H - 1); ++y) {
+        const WT* xr = x + (int64_t)y * im.pitch;
+        float r0 = 0.f, r1 = 0.f;
+#pragma unroll 1
+        for (int c = max(v - R, 0); c <= min(v + R, W - 1); ++c) {
+          const int t = v - c, at = t < 0 ? -t : t;
+          const float h = (float)xr[c] * scale, tg = taps[64 + at];
+          r0 = fmaf(taps[at], h, r0);
+          if (t) r1 = fmaf(t < 0 ? -tg : tg, h, r1);
+        }
+        const int t = o - y, at = t < 0 ? -t : t;
+        const float g = taps[at], tg = taps[64 + at];
+        a = fmaf(g, r0, a);
+        mv = fmaf(g, r1, mv);
+        if (t) mu = fmaf(t < 0 ? -tg : tg, r0, mu);
+      }
+      const int64_t i = map_index(H, o, v);
+      maps[i] = a;
+      maps[im.plane + i] = mu;
+      maps[2 * im.plane + i] = mv;
+      if (v < W) sxd += (double)((float)x[(int64_t)o * im.pitch + v] * a);
+    }
+    if ((o0 + 4) % SX_ROWS == 0 || o0 + 4 >= seg_end) {  // uniform
+      const double tot = wave_sum(sxd);
+      if (lane == 0) part[(int64_t)(o0 / SX_ROWS) * SX_SLOTS] = tot * im.scale;
+      sxd = 0.0;
+    }
+  }
+}
+
+// VEC: FP32 weights, and no group of four columns of this strip straddles the width.
+template <int RA, typename WT, bool VEC>
+__device__ __forceinline__ void cf_segment(const ImageDesc& im, int strip, int s0, int S,
+                                           const char* __restrict__ wbase, char* __restrict__ mbase,
+                                           float* __restrict__ smem) {
+  using G = CfGeom<RA>;
+  float* stage = smem;                   // [2][STAGE]
+  float* ring = smem + 2 * G::STAGE;     // [2][64][RINGP]: R0, R1
+
+  // lane-derived values are recomputed per segment: an opaque thread index
+  // keeps the compiler from hoisting them out of the persistent tile loop
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  const int H = im.H, W = im.W;
+  const int v0 = strip * CONV_TW;
+  const int seg_end = min(s0 + S, H);
+  const int n_out = (seg_end - s0 + CF_CH - 1) / CF_CH;
+  const int nchunks = G::J0 + n_out;
+  const int origin = s0 - RA;  // image row of row 0 of chunk 0
+  const int need_end = min(H, seg_end + RA);
+
+  constexpr uint32_t esz = sizeof(WT);
+  const uint32_t rowbytes = (uint32_t)im.pitch * esz;
+  const rsrc_t wres = make_rsrc(wbase + im.weight_off, (uint32_t)H * rowbytes);
+  const float scale = (float)im.scale;
+
+  // ---- staging: thread item i of a chunk is columns v0 - RA + V d .. + V - 1 of row r ----
+  // Columns left of the image or past the width, rows outside the image and items past the chunk load at an
+  // offset past the end of the buffer, which reads 0 without a memory request. Single columns are dealt to
+  // adjacent lanes (V = 1): 64 x 1024 x 1023 bytes at R = 2 took 216 us as four loads of a group of four.
+  using Unit = std::conditional_t<VEC, f4_t, float>;
+  constexpr int V = VEC ? 4 : 1, PER = G::SW / V;             // columns per item, items per row
+  constexpr int NI = (CF_CH * PER + CF_NT - 1) / CF_NT;       // items per thread and chunk
+  static_assert(V * (NI * CF_NT - CF_CH * PER) <= G::STAGE - CF_CH * G::SWP, "a slot per spare item");
+  int irow[NI], ioff[NI];
+  uint32_t ibyte[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int idx = tid + CF_NT * i;
+    const int r = idx / PER, d = idx - r * PER;
+    const int x = v0 - RA + V * d;
+    const bool item = idx < CF_CH * PER;
+    irow[i] = item && x >= 0 && x < W ? r : -(1 << 30);  // never inside the image
+    ibyte[i] = (uint32_t)x * esz;
+    ioff[i] = item ? r * G::SWP + V * d : CF_CH * G::SWP + V * (idx - CF_CH * PER);
+  }
+  // stored weights of this lane's outputs: row o0 + n, columns c0 .. c0 + 3
+  const int oc = v0 + 16 * wave + 4 * q;
+  Unit pre[NI];
+  f4_t hpre;
+  auto fetch = [&](int j) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int y = origin + j * CF_CH + irow[i];
+      const uint32_t off = y >= 0 && y < need_end ? (uint32_t)y * rowbytes + ibyte[i] : BUF_OOB;
+      if constexpr (VEC)
+        pre[i] = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(wres, off, 0, 0));
+      else
+        pre[i] = (float)buf_load<WT>(wres, off, 0);
+    }
+    const int o = s0 + (j - G::J0) * CF_CH + n;
+    const uint32_t off = o >= s0 && o < seg_end && oc < W ? (uint32_t)o * rowbytes + (uint32_t)oc * esz : BUF_OOB;
+    if constexpr (VEC) {
+      hpre = __builtin_bit_cast(f4_t, __builtin_amdgcn_raw_buffer_load_b128(wres, off, 0, 0));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        hpre[e] = (float)buf_load<WT>(wres, oc + e < W && off < BUF_OOB ? off + (uint32_t)e * esz : BUF_OOB, 0);
+    }
+  };
+
+  // ---- outputs: wave w writes panel 4 strip + w, a 16 x 16 tile per chunk ----
+  const int panel = 4 * strip + wave;
+  const bool pan_ok = panel < im.npanels;  // the strip's last panels may lie past the width
+  const uint32_t planeb = (uint32_t)(im.plane * (int64_t)sizeof(float));
+  const char* mimg = mbase + im.map_off;
+  const rsrc_t resA = make_rsrc(mimg, planeb), resU = make_rsrc(mimg + planeb, planeb),
+               resV = make_rsrc(mimg + 2 * (size_t)planeb, planeb);
+  const uint32_t pan_base = (uint32_t)panel * (uint32_t)H * 64u + 16u * (uint32_t)q;
+  double* part = reinterpret_cast<double*>(mbase + im.map_off + im.part_off) +
+                 ((int64_t)strip * im.nsxg) * SX_SLOTS + wave;
+  float* ring_col = ring + (16 * wave + n) * G::RINGP;
+  double sxd = 0.0;   // this lane's share of the current S_X row group
+  bool odd = false;   // a map value of this wave is not finite
+
+  // the three stores of a column pass, dropped: keeps the sequence of pending memory operations the same
+  // in the prologue and the warm-up chunks, so that the compiler's waits for a chunk's loads leave the
+  // stores after them pending
+  auto pad_stores = [&]() {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int d = 0; d < 3; ++d) __builtin_amdgcn_raw_buffer_store_b32(0u, resA, BUF_OOB + 16u * d, 0, 0);
+    asm volatile("" ::: "memory");
+  };
+
+  fetch(0);
+  pad_stores();
+
+  // ---- taps: step st of lane (n, q) holds f(t), t = n + RA - k ----
+  float g[G::KS], tg[G::KS];
+  {
+    const double k2 = -0.5 / (im.sigma * im.sigma);
+    const double gl = lane <= im.R ? exp(k2 * (double)(lane * lane)) : 0.0;
+    const float gT = (float)gl, tgT = (float)((double)lane * gl);
+#pragma unroll
+    for (int st = 0; st < G::KS; ++st) {
+      const int t = n + RA - k_of<RA>(st, q), at = t < 0 ? -t : t;  // |t| <= 15 + RA < 64
+      const float a = __shfl(gT, at), b = __shfl(tgT, at);
+      g[st] = a;
+      tg[st] = t < 0 ? -b : b;
+    }
+  }
+
+  auto chunk = [&](int j, auto B) {
+    float* xs = stage + decltype(B)::value * G::STAGE;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) *reinterpret_cast<Unit*>(xs + ioff[i]) = pre[i] * scale;
+    const f4_t h = hpre;
+    __syncthreads();
+    fetch(j + 1);  // past the last chunk: rows outside the segment, zeros
+
+    // ---------------- row pass: chunk j -> ring block j mod NB ----------------
+    {
+      const float* xr = xs + n * G::SWP + 16 * wave;
+      f4_t r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
+#pragma unroll
+      for (int s = 0; s < G::NG; ++s) {
+        const f4_t a = *reinterpret_cast<const f4_t*>(xr + 16 * s + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          r0 = mfma(a[e], g[4 * s + e], r0);
+          r1 = mfma(a[e], tg[4 * s + e], r1);
+        }
+      }
+      if constexpr (G::REM) {
+        const f2_t a = *reinterpret_cast<const f2_t*>(xr + 16 * G::NG + 2 * q);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          r0 = mfma(a[e], g[4 * G::NG + e], r0);
+          r1 = mfma(a[e], tg[4 * G::NG + e], r1);
+        }
+      }
+      float* rp = ring_col + (j % G::NB) * CF_CH + 4 * q;
+      *reinterpret_cast<f4_t*>(rp) = r0;
+      *reinterpret_cast<f4_t*>(rp + G::RING) = r1;
+    }
+    // the column pass reads ring rows this wave has just written: keep the
+    // compiler from moving LDS accesses across (the hardware keeps their order)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    const int jo = j - G::J0;
+    if (jo < 0) {  // uniform: warm-up
+      pad_stores();
+      return;
+    }
+
+    // ---------------- column pass: output rows o0..o0+15 ----------------
+    const int o0 = s0 + jo * CF_CH;
+    f4_t am = {0.f, 0.f, 0.f, 0.f}, um = am, vm = am;
+#pragma unroll
+    for (int s = 0; s < G::NG; ++s) {
+      const float* rp = ring_col + (jo + s) % G::NB * CF_CH + 4 * q;
+      const f4_t y0 = *reinterpret_cast<const f4_t*>(rp), y1 = *reinterpret_cast<const f4_t*>(rp + G::RING);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        am = mfma(y0[e], g[4 * s + e], am);
+        um = mfma(y0[e], tg[4 * s + e], um);
+        vm = mfma(y1[e], g[4 * s + e], vm);
+      }
+    }
+    if constexpr (G::REM) {
+      const float* rp = ring_col + (jo + G::NG) % G::NB * CF_CH + 2 * q;
+      const f2_t y0 = *reinterpret_cast<const f2_t*>(rp), y1 = *reinterpret_cast<const f2_t*>(rp + G::RING);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        am = mfma(y0[e], g[4 * G::NG + e], am);
+        um = mfma(y0[e], tg[4 * G::NG + e], um);
+        vm = mfma(y1[e], g[4 * G::NG + e], vm);
+      }
+    }
+    // lane (n, q) holds row o0 + n, columns 16 wave + 4q + i
+    const int row = o0 + n;
+    const bool ok = row < seg_end;
+    const uint32_t off = ok && pan_ok ? pan_base + (uint32_t)row * 64u : BUF_OOB;
+    float sx = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sx = fmaf(h[i], am[i], sx);  // h is 0 past the width and the segment
+    sx = fmaf(0.f, (vm[0] + vm[1]) + (vm[2] + vm[3]), sx);   // not a number if a map value is none or infinite
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, am), resA, off, 0, CF_STREAM);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, um), resU, off, 0, CF_STREAM);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, vm), resV, off, 0, CF_STREAM);
+    sxd += ok ? (double)sx : 0.0;
+    // the last chunk of an S_X row group (or of the segment): one FP64 partial per wave
+    if ((jo + 1) % (SX_ROWS / CF_CH) == 0 || jo == n_out - 1) {  // uniform
+      const double tot = wave_sum(sxd);
+      if (lane == 0) part[(int64_t)(o0 / SX_ROWS) * SX_SLOTS] = tot * im.scale;
+      odd |= !(fabs(tot) < INFINITY);
+      sxd = 0.0;
+    }
+  };
+
+  int j = 0;
+  for (; j + 2 <= nchunks; j += 2) {
+    chunk(j, std::integral_constant<int, 0>{});
+    chunk(j + 1, std::integral_constant<int, 1>{});
+  }
+  if (j < nchunks) chunk(j, std::integral_constant<int, 0>{});
+  if (__builtin_amdgcn_readfirstlane(odd))
+    segment_by_windows<WT>(im, strip, s0, seg_end, wbase, mbase, ring + 16 * wave * G::RINGP);
+}
+
+// One segment for the image's stored weight type (one uniform branch per segment).
+template <int RA>
+__device__ __forceinline__ void cf_segment_any(const ImageDesc& im, int strip, int s0, int S, const char* wbase,
+                                               char* mbase, float* smem) {
+  if (im.wdtype == 1) {
+    if (im.W % 4 == 0 || strip * CONV_TW + CONV_TW + RA <= im.W)
+      cf_segment<RA, float, true>(im, strip, s0, S, wbase, mbase, smem);
+    else
+      cf_segment<RA, float, false>(im, strip, s0, S, wbase, mbase, smem);
+  } else if (im.wdtype == 0) {
+    cf_segment<RA, uint8_t, false>(im, strip, s0, S, wbase, mbase, smem);
+  } else {
+    cf_segment<RA, double, false>(im, strip, s0, S, wbase, mbase, smem);
+  }
+}
+
+template <int RA>
+__global__ void __launch_bounds__(CF_NT, CfGeom<RA>::WGS) conv_f32_image_kernel(ImageDesc im, int S, const char* wbase, char* mbase) {
+  __shared__ __align__(16) float smem[CfGeom<RA>::SMEM / sizeof(float)];
+  const int strip = blockIdx.x % im.nstrips;
+  const int seg = blockIdx.x / im.nstrips;
+  cf_segment_any<RA>(im, strip, seg * S, S, wbase, mbase, smem);
+}
+
+// Persistent launch over the tiles of one radius class: workgroup b walks the
+// sublist of its XCD, b mod CONV_XCDS.
+template <int RA>
+__global__ void __launch_bounds__(CF_NT, CfGeom<RA>::WGS) conv_f32_tiles_kernel(const ImageDesc* __restrict__ images,
+                                                               const ConvTile* __restrict__ tiles, XcdSplit xs,
+                                                               const char* wbase, char* mbase) {
+  __shared__ __align__(16) float smem[CfGeom<RA>::SMEM / sizeof(float)];
+  const int x = blockIdx.x % CONV_XCDS, nx = gridDim.x / CONV_XCDS;
+  const int end = xs.beg[x + 1];
+  for (int i = xs.beg[x] + (int)blockIdx.x / CONV_XCDS; i < end; i += nx) {
+    const ConvTile t = tiles[i];
+    const ImageDesc im = images[t.img];
+    cf_segment_any<RA>(im, t.strip, t.s0, t.S, wbase, mbase, smem);
+    __syncthreads();  // the next tile restages the shared memory
+  }
+}
+
+}  // namespace
+
+#define ITC_FOR_CF(X) X(4) X(8) X(12) X(16) X(20) X(24) X(28) X(32)
+
+hipError_t launch_conv_f32_image(const ImageDesc& im, const void* w, void* m, hipStream_t s) {
+  const int S = conv_segment_rows(im);
+  const dim3 grid(im.nstrips * ((im.H + S - 1) / S));
+#define ITC_CASE(RA)                                                                                \
+  case RA:                                                                                          \
+    hipLaunchKernelGGL((conv_f32_image_kernel<RA>), grid, dim3(CF_NT), 0, s, im, S, (const char*)w, \
+                       (char*)m);                                                                   \
+    return hipGetLastError();
+  switch ((im.rclass + 3) / 4 * 4) { ITC_FOR_CF(ITC_CASE) default: return hipErrorInvalidValue; }
+#undef ITC_CASE
+}
+
+hipError_t launch_conv_f32_tiles(int rclass, const ImageDesc* d_images, const ConvTile* d_tiles, const XcdSplit& xs,
+                                 const void* w, void* m, int grid, hipStream_t s) {
+  if (grid % CONV_XCDS != 0) return hipErrorInvalidValue;
+#define ITC_CASE(RA)                                                                                   \
+  case RA:                                                                                             \
+    hipLaunchKernelGGL((conv_f32_tiles_kernel<RA>), dim3(grid), dim3(CF_NT), 0, s, d_images, d_tiles,  \
+                       xs, (const char*)w, (char*)m);                                                  \
+    return hipGetLastError();
+  switch ((rclass + 3) / 4 * 4) { ITC_FOR_CF(ITC_CASE) default: return hipErrorInvalidValue; }
+#undef ITC_CASE
+}
+
+int conv_f32_blocks_per_cu(int rclass) {
+  int nb = 0;
+  hipError_t e = hipErrorInvalidValue;
+#define ITC_CASE(RA)                                                                            \
+  case RA:                                                                                      \
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, conv_f32_tiles_kernel<RA>, CF_NT, 0); \
+    break;
+  switch ((rclass + 3) / 4 * 4) { ITC_FOR_CF(ITC_CASE) default: break; }
+#undef ITC_CASE
+  return e == hipSuccess ? nb : 0;
+}
+
+}  // namespace itc

@@ -116,11 +116,7 @@ int conv_mx_radius(int rclass);
 // Single image (h_image by value, all strips and segments in one grid).
 hipError_t launch_conv_image(bool f64, const ImageDesc& h_image, const void* weights, void* maps,
                              hipStream_t s);
-// Persistent launch over `ntiles` tiles of one radius class.
-hipError_t launch_conv_tiles(bool f64, int rclass, const ImageDesc* d_images, const ConvTile* d_tiles,
-                             const XcdSplit& xs, const void* weights, void* maps, int grid, hipStream_t s);
 // Resident workgroups per compute unit of the persistent kernels (0 on error).
-int conv_tiles_blocks_per_cu(bool f64, int rclass);
 int fit_blocks_per_cu(bool f64, int m_max, int max_passes);
 // Segment rows used for a single image (multiple of CONV_CH).
 int conv_segment_rows(const ImageDesc& im);
@@ -131,6 +127,12 @@ hipError_t launch_conv_mx_image(const ImageDesc& h_image, const void* weights, v
 hipError_t launch_conv_mx_tiles(int max_ra, const ImageDesc* d_images, const ConvTile* d_tiles, const XcdSplit& xs,
                                 const void* weights, void* maps, int grid, hipStream_t s);
 int conv_mx_blocks_per_cu(int max_ra);
+// FP32 maps that the kernel above does not take: a single image, and one
+// persistent launch over the tiles of one radius class.
+hipError_t launch_conv_f32_image(const ImageDesc& h_image, const void* weights, void* maps, hipStream_t s);
+hipError_t launch_conv_f32_tiles(int rclass, const ImageDesc* d_images, const ConvTile* d_tiles, const XcdSplit& xs,
+                                 const void* weights, void* maps, int grid, hipStream_t s);
+int conv_f32_blocks_per_cu(int rclass);
 // Debug validation (ITC_DEBUG_VALIDATE): the number of non-finite stored
 // weights of one image (h_image) or of n plan images (d_images); waits for
 // the stream.

@@ -203,7 +203,7 @@ struct itc_plan {
   int max_passes = 1;  // largest fit pass count over the images
   std::vector<ImageDesc> images;
   // convolution class keys of the plan (tile shapes are set per key) and its
-  // launches: one per vector-ALU class, one for every matrix-core class
+  // launches: one per FP32 class, one for every matrix-core class
   // together; launch l covers tiles [launch_begin[l], launch_end[l])
   std::vector<ConvTile> tiles;
   std::vector<int> cls;
@@ -235,11 +235,11 @@ struct itc_plan {
   itc::ChamferTask* d_ch_bands = nullptr;
 };
 
-// Convolution tile lists of a plan: per class key (the VALU kernel's radius
+// Convolution tile lists of a plan: per class key (the FP32 kernel's radius
 // class, or CONV_MX_CLASS + aligned radius for the matrix-core kernel), every
 // image's strips cut into segments of about the class's target height
 // (multiples of the S_X row group), sorted by cost, most expensive first. A
-// vector-ALU class is one persistent launch; the matrix-core classes share
+// FP32 class is one persistent launch; the 8-bit classes share
 // one persistent launch, largest radius first (a workgroup then changes its
 // ring layout only a few times), with the fewest workgroups per compute unit
 // any of them asks for. Every launch's tiles are split into one sublist per
@@ -287,7 +287,7 @@ static int class_key_of(const ImageDesc& im) {
 
 static int class_occupancy(const itc_plan* p, int key) {
   const int per = key >= itc::CONV_MX_CLASS ? itc::conv_mx_blocks_per_cu(p->mx_max_ra)
-                                            : itc::conv_tiles_blocks_per_cu(false, key);
+                                            : itc::conv_f32_blocks_per_cu(key);
   return per < 1 ? 1 : per;
 }
 
@@ -572,7 +572,7 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
   if (!p) return fail(ITC_E_DEVICE, "out of host memory");
   p->n = b->n;
   p->images.resize(b->n);
-  // class keys: the VALU kernel's radius class, or CONV_MX_CLASS + aligned
+  // class keys: the FP32 kernel's radius class, or CONV_MX_CLASS + aligned
   // radius for the matrix-core kernel (8-bit weights)
   std::vector<double> fit_cost(b->n);
   for (int i = 0; i < b->n; ++i) {
@@ -770,7 +770,7 @@ itc_status itc_lattice_precompute_batched(itc_plan* p, const void* weights, void
         key >= itc::CONV_MX_CLASS
             ? itc::launch_conv_mx_tiles(key - itc::CONV_MX_CLASS, p->d_images, p->d_tiles + p->launch_begin[l],
                                         p->launch_split[l], weights, maps, p->launch_grid[l], (hipStream_t)stream)
-            : itc::launch_conv_tiles(false, key, p->d_images, p->d_tiles + p->launch_begin[l], p->launch_split[l],
+            : itc::launch_conv_f32_tiles(key, p->d_images, p->d_tiles + p->launch_begin[l], p->launch_split[l],
                                      weights, maps, p->launch_grid[l], (hipStream_t)stream);
     if (e != hipSuccess) return device_fail(e, "batched convolution launch");
   }

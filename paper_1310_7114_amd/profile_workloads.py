@@ -5,7 +5,7 @@ counter runs that ``profsummary`` turns into the summaries under ``profiles/``.
     python3 -m paper_1310_7114_amd.profile_workloads gray2048 [--copy-calib-mib 1024]
 
 * differentiation: 64 weighted 1024 x 1024 gray images (weights g/255 as
-  FP32, M 256, sigma 4): the convolution (vector-ALU kernel, FP32 weights),
+  FP32, M 256, sigma 4): the convolution (FP32 weights),
   D at the initial codebooks, dD/dw and dD/dh.
 * gray2048: the 2048 x 2048 gray image (M 500, sigma 6): its maps and 200
   sweeps of the multi-workgroup fit.

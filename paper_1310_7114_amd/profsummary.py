@@ -42,8 +42,8 @@ GROUPS = {
                             SILHOUETTES, None),
     "conv_silhouettes1400": ("itc::conv_mx_tiles_kernel", [f"{CSRC}/conv_mfma.hip", f"{CSRC}/itc_device.h"],
                              SILHOUETTES, 13.0 * SILHOUETTE_PX),
-    "conv_valu_gray1024x64": ("itc::conv_tiles_kernel", [f"{CSRC}/conv.hip", f"{CSRC}/itc_device.h"],
-                              GRAY1024, 16.0 * GRAY1024_PX),
+    "conv_f32_gray1024x64": ("itc::conv_f32_tiles_kernel", [f"{CSRC}/conv_f32.hip", f"{CSRC}/itc_device.h"],
+                             GRAY1024, 16.0 * GRAY1024_PX),
     "adjoint_gray1024x64": ("itc::grad_weights_tiles_kernel", [f"{CSRC}/adjoint.hip", f"{CSRC}/itc_device.h"],
                             GRAY1024, 8.0 * GRAY1024_PX),
     "fit_wide_gray2048": ("itc::fit_wide_kernel", [f"{CSRC}/fit_wide.hip", f"{CSRC}/itc_device.h"],

@@ -126,6 +126,47 @@ def test_maps_float_weights_with_pitch(gpu_lib):
         assert normwise(g, r) <= 1e-5
 
 
+@pytest.mark.parametrize("wdtype", [np.float32, np.float64, np.uint8], ids=["f32", "f64", "u8"])
+@pytest.mark.parametrize("R", [1, 4, 5, 8, 12, 13, 17, 24, 25, 32])
+def test_maps_fp32_window_edges(gpu_lib, R, wdtype):
+    """Windows of every aligned radius, tile remainders in both directions, segment and strip ends, rows that
+    are not 16-byte aligned. A map value is two nested sums of at most 2 (R + 3) + 16 FP32 products each,
+    every one rounded a few times: its error is within that count of half-ulps of the sum of magnitudes."""
+    rng = np.random.default_rng(R)
+    sigma = R / 3.0
+    t = np.abs(O.taps(sigma, R))
+    for H, W in [(1, 1), (15, 17), (16, 64), (17, 65), (31, 128), (33, 61), (64 + 2 * R, 130), (321, 19)]:
+        img = rng.integers(0, 256, (H, W)).astype(np.uint8) if wdtype == np.uint8 else rng.uniform(0, 1, (H, W)).astype(wdtype)
+        _, got, sx = gpu_maps(gpu_lib, img, sigma, 0.5, R, aligned=False)
+        I = img.astype(np.float64) * 0.5
+        g, tg = t, t * np.abs(np.arange(-R, R + 1))
+        mags = [O.correlate_axis(O.correlate_axis(I, a, 0), b, 1) for a, b in ((g, g), (tg, g), (g, tg))]
+        ref = ref_maps(I, sigma, R)
+        for x, r, m in zip(got, ref, mags):
+            assert np.all(np.abs(x - r) <= (2 * (2 * (R + 3) + 16) + 8) * 2.0 ** -24 * m + 1e-12)
+        assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("R", [4, 12, 24])
+def test_maps_fp32_nonfinite_reach(gpu_lib, R, value):
+    """A weight that is not finite, or overflows in a sum, changes the pixels within R of it only."""
+    rng = np.random.default_rng(R)
+    img = rng.uniform(0, 1, (150, 141)).astype(np.float32)
+    for u, v in [(0, 0), (64, 63), (149, 140), (77, 130)]:
+        bad = img.copy()
+        bad[u, v] = value
+        clean = img.copy()
+        clean[u, v] = 0.0
+        _, got, _ = gpu_maps(gpu_lib, bad, R / 3.0, 1.0, R)
+        near = np.zeros(img.shape, bool)
+        near[max(u - R, 0): u + R + 1, max(v - R, 0): v + R + 1] = True
+        for x, r in zip(got, ref_maps(clean.astype(np.float64), R / 3.0, R)):
+            assert normwise(np.where(near, 0.0, x), np.where(near, 0.0, r)) <= 1e-5
+        if not np.isfinite(value):
+            assert not np.isfinite(got[0][near]).any()
+
+
 def test_maps_full_size_512(gpu_lib):
     case = S.config2_case()
     _, got, sx = gpu_maps(gpu_lib, case.img, case.sigma)
