@@ -288,20 +288,24 @@ __global__ void __launch_bounds__(CH_ROWS_NT) chamfer_rows_batched_kernel(const 
 // and the exact T of the seam rows 32, 64, .. (every path that crosses a seam on
 // a diagonal step: T(p) = b m + T(p + m f) there). Three kernels:
 //   * edges: bit masks of whole columns give, at every seam row, the distances
-//     up and down the column to the background;
+//     up and down the column to the background, and stay in the output's row
+//     below each seam, one word per column, for the bands;
 //   * seams: T of the seam rows by the row search of the other form (1 / 32 of
 //     its work), kept as T | up in the seam's row of the output and T | down in
 //     the row above it, which the bands of those rows own;
-//   * bands: one workgroup per band reads its 32 rows of the image, E goes to
-//     LDS as 16-bit integers, and one thread per diagonal scans its 33 entries
+//   * bands: one workgroup per band reads its rows' bit words (a single band or a
+//     single row: the image), E goes to LDS as 16-bit integers, and one thread per diagonal scans its 33 entries
 //     both ways in registers, first along one diagonal in place, then along the
 //     other out to T. (The second scan starts from the first one's result: a
 //     path with steps along both diagonals is a path too.) Outside the lattice E
 //     is 0. The row stride of E is an odd number of words, so that 32 lanes on
 //     32 rows meet 32 banks.
-// Traffic: the image twice and T once, 6 B/px. Measured on 1,400 silhouettes
-// (369 Mpx): 0.74 ms (edges 0.16, seams 0.07, bands 0.52: 2.2 GB at 4.3 TB/s)
-// against 2.42 ms of the column and row passes (0.34 + 2.10).
+// Traffic: the image and T once and 3/32 words per pixel of edges, 5.4 B/px.
+// Measured on 1,400 silhouettes (355 Mpx): 0.62 ms (edges 0.12, seams 0.07, bands
+// 0.43) against 2.42 ms of the column and row passes (0.34 + 2.10). T goes out
+// in non-temporal stores: ordinary ones took 0.52 ms in the bands and 0.04 ms
+// in the next call's edges, whose reads evict them; without stores the bands take
+// 0.37 ms, issue bound (bit words to E 0.21, the diagonals 0.16).
 // ---------------------------------------------------------------------------
 constexpr int CHB_ROWS = 32;
 constexpr int CHB_NT = 512;
@@ -342,7 +346,8 @@ extern "C" __device__ int itc_writelane(int x, int l, int v) __asm("llvm.amdgcn.
 
 __device__ __forceinline__ uint32_t rows_mask(int n) { return n >= 32 ? ~0u : (1u << n) - 1u; }
 
-// Edges of one strip of 64 columns: at each seam row 32 w, up | down << 16.
+// Edges of one strip of 64 columns: at each seam row 32 w, up | down << 16, and
+// in the row after it the bit word of the column's rows 32 w .. 32 w + 31.
 __device__ __forceinline__ void chamfer_edges(const uint8_t* __restrict__ x, int64_t pitch, float* __restrict__ t,
                                               int H, int W, int v0, uint32_t* __restrict__ sbits,
                                               uint16_t* __restrict__ sup, uint16_t* __restrict__ sdown) {
@@ -351,9 +356,26 @@ __device__ __forceinline__ void chamfer_edges(const uint8_t* __restrict__ x, int
   const bool col = j < W;
   const rsrc_t xr = make_rsrc(x, (uint32_t)((int64_t)H * pitch));
   const int nw = (H + 31) / 32;
+  const bool quads = (((uintptr_t)x | (uintptr_t)pitch) & 3u) == 0;  // rows start 4-byte aligned (uniform)
   for (int w = wave; w < nw; w += CH_COLS_WAVES) {
-    uint32_t v[32];
     const int n = min(32, H - 32 * w);
+    if (quads) {
+      // lane (q, c): four columns 4c .. 4c + 3 of rows 8q .. 8q + 7, whose bits are a byte of each column's word
+      const int q = lane >> 4, c = 4 * (lane & 15);
+      const uint32_t off = (uint32_t)(32 * w + 8 * q) * (uint32_t)pitch + (uint32_t)(v0 + c);
+      uint32_t v[8], acc = 0u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        v[k] = buf_load<uint32_t>(xr, 8 * q + k < n && v0 + c < W ? off + (uint32_t)k * (uint32_t)pitch : BUF_OOB, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        acc = acc >> 1 | ((((v[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[k]) & 0x80808080u);
+      uint8_t* sb = reinterpret_cast<uint8_t*>(sbits + w * 64 + c) + q;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sb[4 * e] = (uint8_t)(acc >> (8 * e));
+      continue;
+    }
+    uint32_t v[32];
     load_rows(xr, pitch, 32 * w, n, j, col, v);
     uint32_t m = 0u;
 #pragma unroll
@@ -378,8 +400,10 @@ __device__ __forceinline__ void chamfer_edges(const uint8_t* __restrict__ x, int
   }
   __syncthreads();
   if (col) {
-    for (int w = 1 + wave; w < nw; w += CH_COLS_WAVES)
-      t_word(t, pitch, 32 * w)[j] = (uint32_t)sup[w * 64 + lane] | (uint32_t)sdown[w * 64 + lane] << 16;
+    for (int w = wave; w < nw; w += CH_COLS_WAVES) {
+      if (w > 0) t_word(t, pitch, 32 * w)[j] = (uint32_t)sup[w * 64 + lane] | (uint32_t)sdown[w * 64 + lane] << 16;
+      if (32 * w + 1 < H) t_word(t, pitch, 32 * w + 1)[j] = sbits[w * 64 + lane];
+    }
   }
   __syncthreads();  // LDS is reused by the next strip
 }
@@ -431,6 +455,7 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
   const int ns = (W + 63) / 64;
   const bool first = r0 == 0, last = r0 + CHB_ROWS >= H;
   const int n = min(CHB_ROWS, H - r0);
+  const bool words = H > CHB_ROWS && n > 1;  // the edges pass left the columns' bit words in row r0 + 1
   const rsrc_t xr = make_rsrc(x, (uint32_t)((int64_t)H * pitch));
   // guard columns of E: outside the lattice, background
   for (int q = tid; q < (CHB_ROWS + 1) * 2 * CHB_ROWS; q += CHB_NT) {
@@ -444,23 +469,27 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
   for (int st = wave; st < ns; st += CHB_WAVES) {
     const int j = 64 * st + lane;
     const bool col = j < W;
-    uint32_t v[32];
-    load_rows(xr, pitch, r0, n, j, col, v);
+    uint32_t m = 0u, lo = 0u, hi = 0u;
+    if (words) {
+      if (col) m = t_word(t, pitch, r0 + 1)[j];
+    } else {
+      uint32_t v[32];
+      load_rows(xr, pitch, r0, n, j, col, v);
+#pragma unroll
+      for (int k = 0; k < 32; ++k) m |= (v[k] != 0u ? 1u : 0u) << k;
+      m &= rows_mask(n);
+    }
     uint32_t top = 0u, bot = 0u;  // T | up of the first row, T | down of the seam below
     if (col && !first) top = t_word(t, pitch, r0)[j];
     if (col && !last) bot = t_word(t, pitch, r0 + CHB_ROWS - 1)[j];
-    uint32_t m = 0u, lo = 0u, hi = 0u;
     for_each_index(
         [&](auto kk) {
           constexpr int k = decltype(kk)::value;
-          const uint64_t row = __ballot(v[k] != 0u);
-          m |= (v[k] != 0u ? 1u : 0u) << k;
+          const uint64_t row = __ballot((m & (1u << k)) != 0u);
           lo = (uint32_t)itc_writelane((int)(uint32_t)row, k, (int)lo);  // lane k keeps row k's words
           hi = (uint32_t)itc_writelane((int)(uint32_t)(row >> 32), k, (int)hi);
         },
         std::make_integer_sequence<int, 32>{});
-    m &= rows_mask(n);
-    if (lane >= n) lo = hi = 0u;
     const bool some_fg = __any(m != 0u);  // uniform
     if (some_fg && lane == 0) atomicOr(fg, 1u << st);
     if (lane < CHB_ROWS) {
@@ -569,7 +598,7 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
       // opaque, so that no part of it becomes the instruction's own offset: the sum of the two does not wrap
       uint32_t off = (uint32_t)(s - i) * 4u;
       asm("" : "+v"(off));
-      buf_store((float)T, rr, off, 0);
+      buf_stream((float)T, rr, off, 0);
       tr += pitch;
     }
   }
@@ -599,8 +628,12 @@ __global__ void __launch_bounds__(CH_COLS_NT) chamfer_edges_batched_kernel(const
                                                                            int ntasks, const uint8_t* x, float* t) {
   __shared__ uint32_t sbits[CH_WORDS * 64];
   __shared__ uint16_t sup[CH_WORDS * 64], sdown[CH_WORDS * 64];
-  for (int k = blockIdx.x; k < ntasks; k += gridDim.x) {
-    const ChamferTask c = tasks[k];
+  for (int k = blockIdx.x; k < (ntasks + 63) / 64 * 64; k += gridDim.x) {
+    // workgroups b, b + 8, .. share an XCD: it takes runs of eight strips, whose rows share cache lines
+    // (0.155 ms of edges for 0.165 one strip apart)
+    const int kt = (k & ~63) + 8 * (k & 7) + (k >> 3 & 7);
+    if (kt >= ntasks) continue;
+    const ChamferTask c = tasks[kt];
     const ImageDesc& im = images[c.img];
     if (im.H <= CHB_ROWS) continue;  // one band, no seam (uniform)
     chamfer_edges(x + im.weight_off, im.pitch, t + im.weight_off, im.H, im.W, c.pos * 64, sbits, sup, sdown);

@@ -199,6 +199,14 @@ __device__ __forceinline__ void buf_store(T v, rsrc_t r, uint32_t voff, uint32_t
                                           r, voff, soff, 0);
 }
 
+// Store of a 32-bit result that nothing of this launch reads: non-temporal, so
+// that it leaves no dirty lines in the caches for what follows to evict.
+template <typename T>
+__device__ __forceinline__ void buf_stream(T v, rsrc_t r, uint32_t voff, uint32_t soff) {
+  static_assert(sizeof(T) == 4, "32-bit results");
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 2);
+}
+
 // Deterministic FP64 sum of n values by one workgroup of nt threads (nt a
 // multiple of 64): thread t adds t, t+nt, ...; then each wave by a fixed xor
 // tree; then the waves in order. `red` is shared scratch of nt/64 doubles.
