@@ -161,14 +161,20 @@ __device__ __forceinline__ int pair_units(int M) {
   return units;
 }
 
-// The pair phase of one sweep: wave `wave` walks its share [ua, ub) of the
-// chunk steps and writes each visited codevector's E to part[wave * M + k]
-// (consecutive lanes meet consecutive words). Returns this lane's sum of its C
-// terms.
-template <typename T>
-__device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, V2<T>* __restrict__ part, int M, int ua, int ub,
-                                             int wave, int lane) {
-  double csum = 0.0;
+// A wave's share [ua, ub) of the chunk steps, as the chunks it visits: lane i
+// keeps visit i (at most 18: 16 full chunks and the remainder's two). They are laid
+// out once per image: finding the chunks in every sweep's scalar code took 0.33 of
+// 2.44 us a sweep at M = 100, 0.37 of 4.98 at M = 200, 27 of 668 us of 1,400 silhouettes.
+// Reading a visit's first entries ahead of the one before it costs more registers
+// than it saves (2.34 us, 4.98).
+struct Visits {
+  int n = 0;
+  uint32_t where = 0;  // first codevector | size << 16 | log2 P << 24
+  uint32_t steps = 0;  // first unit | units << 16
+};
+
+__device__ __forceinline__ Visits pair_visits(int M, int ua, int ub, int lane) {
+  Visits v;
   int cu0 = 0, k0 = 0;
   while (k0 < M && cu0 < ub) {  // uniform
     int size = 0;
@@ -176,25 +182,43 @@ __device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, V2<T>
     const int nu = chunk_units(M, lg);
     const int s0 = ua > cu0 ? ua : cu0, s1 = ub < cu0 + nu ? ub : cu0 + nu;
     if (s0 < s1) {
-      const int k = k0 + (lane >> lg), p = lane & ((1 << lg) - 1);
-      const int u0 = s0 - cu0, u1 = s1 - cu0;
-      T C = 0, Cu = 0, Cv = 0;
-      switch (lg) {
-        case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, C, Cu, Cv); break;
-        default: pair_chunk<T, 64>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      if (lane == v.n) {
+        v.where = (uint32_t)k0 | (uint32_t)size << 16 | (uint32_t)lg << 24;
+        v.steps = (uint32_t)(s0 - cu0) | (uint32_t)(s1 - s0) << 16;
       }
-      if (k < k0 + size) csum += (double)C;  // lanes past the chunk read padding and are idle
-      if (p == 0 && k < k0 + size) {
-        part[wave * M + k] = V2<T>{Cu, Cv};
-      }
+      ++v.n;
     }
     cu0 += nu;
     k0 += size;
+  }
+  return v;
+}
+
+// The pair phase of one sweep: the wave's visits, each visited codevector's E
+// to part[wave * M + k] (consecutive lanes meet consecutive words). Returns this
+// lane's sum of its C terms.
+template <typename T>
+__device__ __forceinline__ double pair_phase(const V2<T>* __restrict__ Wh, V2<T>* __restrict__ part, int M,
+                                             const Visits& vis, int wave, int lane) {
+  double csum = 0.0;
+#pragma unroll 1
+  for (int i = 0; i < vis.n; ++i) {  // uniform
+    const uint32_t where = __builtin_amdgcn_readlane(vis.where, i), steps = __builtin_amdgcn_readlane(vis.steps, i);
+    const int k0 = (int)(where & 0xffffu), size = (int)(where >> 16 & 0xffu), lg = (int)(where >> 24);
+    const int u0 = (int)(steps & 0xffffu), u1 = u0 + (int)(steps >> 16);
+    const int k = k0 + (lane >> lg), p = lane & ((1 << lg) - 1);
+    T C = 0, Cu = 0, Cv = 0;
+    switch (lg) {
+      case 0: pair_chunk<T, 1>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      case 1: pair_chunk<T, 2>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      case 2: pair_chunk<T, 4>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      case 3: pair_chunk<T, 8>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      case 4: pair_chunk<T, 16>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      case 5: pair_chunk<T, 32>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+      default: pair_chunk<T, 64>(Wh, k, p, u0, u1, C, Cu, Cv); break;
+    }
+    if (k < k0 + size) csum += (double)C;  // lanes past the chunk read padding and are idle
+    if (p == 0 && k < k0 + size) part[wave * M + k] = V2<T>{Cu, Cv};
   }
   return csum;
 }
@@ -498,6 +522,7 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
   cm.W = im.W;
   const bool need_d = a.d_trace != nullptr || a.d_out != nullptr || a.status != nullptr;
   const int units = pair_units(M), ua = units * wave / FIT_WAVES, ub = units * (wave + 1) / FIT_WAVES;
+  const Visits vis = pair_visits(M, ua, ub, lane);
   Cell<T> cell[MAXPASS];
   TraceRing ring;
 
@@ -518,7 +543,7 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
     }
 
     // ---- codebook terms of every codevector (scaled coordinates) ----
-    double sw = pair_phase<T>(Wh, part, M, ua, ub, wave, lane);
+    double sw = pair_phase<T>(Wh, part, M, vis, wave, lane);
 
     // ---- A_k and g_k of the owned codevectors; this wave's shares of S_XW and S_W in FP64 ----
     T Ak[MAXPASS], gu[MAXPASS], gv[MAXPASS];
