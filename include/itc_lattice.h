@@ -122,7 +122,7 @@ size_t itc_lattice_maps_bytes(const itc_lattice_desc* d);
  * `maps` at itc_lattice_maps_bytes(d) bytes (written), `s_x` at one double
  * (written). Map columns beyond `width` inside the last panel get unspecified
  * values. 8-bit weights whose rows start 4-byte aligned (base and pitch) take
- * the matrix-core convolution, others the vector-ALU one (same maps to
+ * the FP16-split convolution, other FP32 maps the FP32 one (same maps to
  * rounding).
  */
 itc_status itc_lattice_precompute(const itc_lattice_desc* d, const void* weights, void* maps,
@@ -401,7 +401,7 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out);
 /*
  * Convolution maps and S_X partials of every image: one persistent launch
  * per radius class. 8-bit images whose weight_off and pitch are multiples of
- * 4 take the matrix-core convolution; the weights base must then be 4-byte
+ * 4 take the FP16-split convolution; the weights base must then be 4-byte
  * aligned (ITC_E_ARG otherwise).
  */
 itc_status itc_lattice_precompute_batched(itc_plan* p, const void* weights, void* maps, void* stream);
@@ -467,11 +467,11 @@ int32_t itc_lattice_plan_size(const itc_plan* p);
 /*
  * Tile shapes of a plan's convolution (the batched form of Section 3.1's
  * convolutions), for autotuning. The tiles of a radius class are 64-column
- * strips cut into segments of about `seg_rows` rows. Each vector-ALU class
- * runs one persistent launch with `blocks_per_cu` workgroups per compute
- * unit; the matrix-core classes share one persistent launch, with the
- * smallest `blocks_per_cu` set on any of them. The maps do not depend on the
- * shape (bitwise).
+ * strips cut into segments of about `seg_rows` rows. Each FP32 class (FP32 and
+ * FP64 weights, unaligned 8-bit rows) runs one persistent launch with
+ * `blocks_per_cu` workgroups per compute unit; the classes of aligned 8-bit
+ * rows share one persistent launch, with the smallest `blocks_per_cu` set on
+ * any of them. The maps do not depend on the shape (bitwise).
  *
  * itc_lattice_plan_conv_classes: number of classes, -1 if p is NULL.
  * itc_lattice_plan_conv_class: class c's key (stable identifier), current
@@ -480,15 +480,16 @@ int32_t itc_lattice_plan_size(const itc_plan* p);
  *   ITC_E_NULL for a NULL plan, ITC_E_ARG for c out of range.
  * itc_lattice_plan_set_conv_shape: sets the class with key `key` to
  *   `seg_rows` (64..4096, rounded up to a multiple of 64 per image; 0 = the
- *   default 256) and `blocks_per_cu` (1..the maximum; 0 = the maximum), and
- *   rebuilds and uploads its tile list (synchronous). ITC_E_ARG for an
- *   unknown key or out-of-range values. Plan set-up, not a per-call
- *   operation: no call on the plan may be in flight, and a graph captured
- *   before the change keeps the old launch shapes, so capture after tuning.
+ *   default 256) and `blocks_per_cu` (1..the maximum, or 4 for an FP32 class,
+ *   of which the maximum runs; 0 = the maximum), and rebuilds and uploads its
+ *   tile list (synchronous). ITC_E_ARG for an unknown key or out-of-range
+ *   values. Plan set-up, not a per-call operation: no call on the plan may be
+ *   in flight, and a graph captured before the change keeps the old launch
+ *   shapes, so capture after tuning.
  */
 int32_t itc_lattice_plan_conv_classes(const itc_plan* p);
-/* Kernel launches of the plan's convolution (one per vector-ALU class, one for
- * all matrix-core classes together); -1 if p is NULL. */
+/* Kernel launches of the plan's convolution (one per FP32 class, one for all
+ * classes of aligned 8-bit rows together); -1 if p is NULL. */
 int32_t itc_lattice_plan_conv_launches(const itc_plan* p);
 itc_status itc_lattice_plan_conv_class(const itc_plan* p, int32_t c, int32_t* key, int32_t* seg_rows,
                                        int32_t* blocks_per_cu, int32_t* max_blocks_per_cu);

@@ -693,11 +693,12 @@ itc_status itc_lattice_plan_set_conv_shape(itc_plan* p, int32_t key, int32_t seg
     return fail(ITC_E_ARG, "class key %d is not a convolution class of this plan", key);
   if (seg_rows != 0 && (seg_rows < PLAN_SEG_MIN || seg_rows > PLAN_SEG_MAX))
     return fail(ITC_E_ARG, "segment rows %d outside [%d, %d]", seg_rows, PLAN_SEG_MIN, PLAN_SEG_MAX);
-  if (blocks_per_cu < 0 || blocks_per_cu > class_occupancy(p, key))
-    return fail(ITC_E_ARG, "workgroups per compute unit %d outside [0, %d]", blocks_per_cu,
-                class_occupancy(p, key));
+  // shapes tuned for kernels of which four workgroups fitted a unit stay valid for the FP32 classes
+  const int top = class_occupancy(p, key), most = key < itc::CONV_MX_CLASS ? std::max(top, 4) : top;
+  if (blocks_per_cu < 0 || blocks_per_cu > most)
+    return fail(ITC_E_ARG, "workgroups per compute unit %d outside [0, %d]", blocks_per_cu, most);
   p->key_seg[key] = seg_rows;
-  p->key_per[key] = blocks_per_cu;
+  p->key_per[key] = std::min(blocks_per_cu, top);
   build_conv_tiles(p);
   if (p->tiles.size() > p->tile_cap) return fail(ITC_E_DEVICE, "tile list exceeds its capacity");
   hipError_t e = hipMemcpy(p->d_tiles, p->tiles.data(), sizeof(ConvTile) * p->tiles.size(), hipMemcpyHostToDevice);

@@ -35,6 +35,22 @@ def test_maps_do_not_depend_on_the_tile_shape(gpu_lib):
         assert torch.equal(maps_now(plan), ref), (seg, per)
 
 
+def test_fp32_classes_take_earlier_shapes(gpu_lib):
+    """FP32 weights of every radius: up to four workgroups a unit are accepted, and the maps stay the same."""
+    radii = [2, 8, 12, 16, 24, 32]
+    g = torch.Generator().manual_seed(5)
+    imgs = [torch.rand((90 + 67 * i, 100 + 31 * i), generator=g) for i in range(6)]
+    plan = gpu_lib.BatchPlan(imgs, [2] * 6, [r / 3 for r in radii], [1] * 6, radii=radii)
+    classes = plan.conv_classes()
+    assert [c["key"] for c in classes] == radii
+    ref = maps_now(plan)
+    for seg, per in ((64, 4), (128, 1), (512, 3), (256, 4)):
+        for c in classes:
+            plan.set_conv_shape(c["key"], seg, per)
+        assert all(c["blocks_per_cu"] <= c["max_blocks_per_cu"] for c in plan.conv_classes())
+        assert torch.equal(maps_now(plan), ref), (seg, per)
+
+
 def test_tuned_plan_gives_the_default_results(gpu_lib, tmp_path):
     cases = S.config3_cases(indices=range(3, 1400, 14))
     plan, w0 = make_plan(gpu_lib, cases)
