@@ -136,6 +136,17 @@ def test_literal_equal_widths_and_theta(gpu_lib):
     assert np.array_equal(w2, Ws[-1])
 
 
+@pytest.mark.parametrize("H,W,M,omega", [(97, 131, 600, 14.0), (33, 200, 40, 6.0), (150, 47, 9, 20.0)])
+def test_literal_windows_and_borders(gpu_lib, H, W, M, omega):
+    """Windows of several panels and row chunks, more codevectors than threads, codevectors in the corners, on
+    the borders and on one point, windows larger than the image: each sweep against the oracle."""
+    rng = np.random.default_rng(M)
+    img = rng.integers(0, 256, (H, W)).astype(np.uint8)
+    w0 = np.stack([rng.integers(0, H, M), rng.integers(0, W, M)], axis=1).astype(np.float64)
+    w0[:6] = [[0, 0], [H - 1, 0], [0, W - 1], [H - 1, W - 1], [H // 2, 0], [H // 2, 0]]
+    check_gpu_trajectory(gpu_lib, S.LatticeCase(img, 1 / 255, w0, 2.0, 6, 3), 2.0, omega, 3)
+
+
 def test_literal_zero_sweeps_and_clamp(gpu_lib):
     case = S.config1_case(2)
     xi, om = O.paper_widths(float(case.img.sum()), case.M)

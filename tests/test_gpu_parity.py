@@ -210,6 +210,43 @@ def test_fit_config1_fp32(gpu_lib, seed):
     assert np.abs(tr - tr_ref).max() <= 1e-5 * max(1.0, abs(tr_ref).max())
 
 
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64, 65, 96, 129, 255, 256, 257, 513])
+def test_fit_codebook_layouts_fp64(gpu_lib, M):
+    """Codebook sizes at the edges of the fit's layouts (2 to 16 lanes of one wave, four waves' shares of the
+    chunks, owner passes), two codevectors off the data (frozen) included when M allows: 6 sweeps."""
+    rng = np.random.default_rng(M)
+    img = rng.integers(0, 256, (96, 112)).astype(np.uint8)
+    w0 = rng.uniform([2, 2], [93, 109], (M, 2))
+    if M >= 16:
+        w0[-2:] = [[-40.0, 10.0], [200.0, 200.0]]
+    case = S.LatticeCase(img, 1 / 255, w0, 2.0, 6, 6)
+    _, w, tr, done = run_fit(gpu_lib, case, torch.float64)
+    W_ref, tr_ref, _, _ = O.fit_lattice(case.weights, w0, 2.0, 6, 6)
+    assert done == 6
+    assert wdist(w, W_ref) <= 1e-9
+    if M >= 16:
+        assert np.array_equal(w[-2:], w0[-2:])
+    assert np.abs(tr - tr_ref).max() <= 1e-10 * max(1.0, abs(tr_ref).max())
+
+
+@pytest.mark.parametrize("M", [7, 40])
+def test_fit_trace_lengths_fp64(gpu_lib, M):
+    """The D trace of runs that end before, at and after every 64th sweep, by count and by theta."""
+    rng = np.random.default_rng(M)
+    img = rng.integers(0, 256, (64, 72)).astype(np.uint8)
+    case = S.LatticeCase(img, 1 / 255, rng.uniform([4, 4], [60, 68], (M, 2)), 3.0, 9, 130)
+    _, _, full, _ = run_fit(gpu_lib, case, torch.float64)
+    _, tr_ref, _, _ = O.fit_lattice(case.weights, case.w0, 3.0, 9, 130)
+    assert np.abs(full - tr_ref).max() <= 1e-9 * max(1.0, abs(tr_ref).max())
+    for n in (0, 1, 62, 63, 64, 65, 127, 128):
+        _, _, tr, done = run_fit(gpu_lib, case, torch.float64, iters=n)
+        assert done == n and np.array_equal(tr[:n + 1], full[:n + 1])
+    for theta in (0.05, 0.005):
+        _, _, tr, done = run_fit(gpu_lib, case, torch.float64, theta=theta)
+        _, _, done_ref, _ = O.fit_lattice(case.weights, case.w0, 3.0, 9, 130, theta=theta)
+        assert abs(done - done_ref) <= 1 and np.array_equal(tr[:done + 1], full[:done + 1])
+
+
 def test_one_step_config2(gpu_lib):
     case = S.config2_case()
     maps_ref = O.lattice_maps(case.weights, case.sigma, case.R)
@@ -381,6 +418,23 @@ def test_fit_wide_ragged_codebooks(gpu_lib, M):
     if M >= 16:
         assert np.array_equal(w[-2:], w0[-2:])
     assert np.abs(tr - tr_ref).max() <= 1e-5 * max(1.0, abs(tr_ref).max())
+
+
+@pytest.mark.parametrize("M", [256, 512, 513, 1024])
+def test_fit_wide_codevectors_per_lane(gpu_lib, M):
+    """Codebooks at the edges of the sweep kernel's owner passes, for 4 sweeps with the trace and theta off,
+    and the stop by theta."""
+    case = S.config2_case()
+    on = np.argwhere(case.img > 0)
+    w0 = on[np.random.default_rng(M).choice(len(on), size=M, replace=False)].astype(np.float64) + 0.25
+    c = S.LatticeCase(case.img, case.scale, w0, case.sigma, case.R, 4)
+    m, w, tr, done = run_fit_wide(gpu_lib, c)
+    W_ref, tr_ref, _, _ = O.fit_lattice(case.weights, w0, case.sigma, case.R, 4)
+    assert done == 4
+    assert wdist(w, W_ref) <= 1e-3
+    assert np.abs(tr - tr_ref).max() <= 1e-5 * max(1.0, abs(tr_ref).max())
+    _, _, tr1, done1 = run_fit_wide(gpu_lib, c, theta=1e3, maps=m)
+    assert done1 == 1 and np.array_equal(tr1[:2], tr[:2])
 
 
 def test_fit_wide_zero_iterations_and_alias(gpu_lib):

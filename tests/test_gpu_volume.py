@@ -105,6 +105,22 @@ def test_volume_fit_lane_layouts(gpu_lib, M):
     assert np.abs(tr.cpu().numpy() - tr_ref).max() <= 1e-5 * max(1.0, abs(tr_ref).max())
 
 
+@pytest.mark.parametrize("M", [4, 5, 8, 9, 16, 17, 32, 33, 65, 128, 129, 256, 257, 512, 513, 1024])
+def test_volume_fit_workgroup_sizes(gpu_lib, M):
+    """Codebooks at the edges of the fit's workgroup sizes (64 to 1,024 threads) and lanes per codevector, for
+    2 sweeps, and the stop by theta."""
+    case = S.volume_case(5, D=32, H=40, W=48, M=M, iters=2)
+    m, _, _ = gpu_maps(gpu_lib, case.vol, case.sigma)
+    W_ref, tr_ref, _, _ = O.fit_volume(case.weights, case.w0, case.sigma, case.R, case.iters)
+    w, tr, done = gpu_lib.volume_fit(m, torch.from_numpy(case.w0).cuda(), case.iters)
+    w1, tr1, done1 = gpu_lib.volume_fit(m, torch.from_numpy(case.w0).cuda(), case.iters, theta=1e3)
+    torch.cuda.synchronize()
+    assert int(done.cpu()[0]) == 2 and int(done1.cpu()[0]) == 1
+    assert float(np.linalg.norm(w.cpu().double().numpy() - W_ref, axis=1).max()) <= 1e-3
+    assert np.abs(tr.cpu().numpy() - tr_ref).max() <= 1e-5 * max(1.0, abs(tr_ref).max())
+    assert np.array_equal(tr1.cpu().numpy()[:2], tr.cpu().numpy()[:2])
+
+
 def test_volume_rejects(gpu_lib):
     x = torch.ones((4, 4, 4), dtype=torch.uint8, device="cuda")
     with pytest.raises(gpu_lib.ItcError):
