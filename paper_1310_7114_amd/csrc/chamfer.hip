@@ -159,6 +159,7 @@ __device__ __forceinline__ void chamfer_cols_bits(const uint8_t* __restrict__ x,
 }
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // Least cost over a row of g (LDS, CH_GUARD zeros on each side) from column j,
 // both sides in the halves of packed 16-bit registers.
@@ -557,49 +558,51 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
     }
   }
   __syncthreads();
-  // ---- scans along the diagonals j - i = d, in place ----
+  // ---- scans along the diagonals j - i = d, then along j + i = s, in place ----
   // A task of 64 diagonals reads columns d0 - 32 .. d0 + 63 (strips d0 / 64 - 1 and d0 / 64); without
   // foreground there, all it reads is 0.
-  auto empty = [&](int d0) { return (((uint64_t)strips << 1) >> (d0 >> 6) & 3u) == 0; };
   const u16x2 B2 = {(uint16_t)b, (uint16_t)b};
-  for (int d0 = 64 * wave; d0 < W + CHB_ROWS; d0 += CHB_NT) {
-    if (empty(d0)) continue;
-    const int d = d0 + lane;  // entry (i, d + i) of the guarded rows
-    if (d < W + CHB_ROWS) {
-      uint16_t* e = E + d;
-      u16x2 f[CHB_ROWS + 1];
-      scan_both(e, P + 1, B2, f);
+  auto scan = [&](uint16_t* row0, int st) __attribute__((always_inline)) {
+    for (int d0 = 64 * wave; d0 < W + CHB_ROWS; d0 += CHB_NT) {
+      if ((((uint64_t)strips << 1) >> (d0 >> 6) & 3u) == 0) continue;
+      const int d = d0 + lane;
+      if (d < W + CHB_ROWS) {
+        uint16_t* e = row0 + d;
+        u16x2 f[CHB_ROWS + 1];
+        scan_both(e, st, B2, f);
 #pragma unroll
-      for (int i = 0; i <= CHB_ROWS / 2; ++i) {
-        const u16x2 r = __builtin_elementwise_min(f[i], f[CHB_ROWS - i].yx);
-        e[i * (P + 1)] = r.x;
-        e[(CHB_ROWS - i) * (P + 1)] = r.y;
+        for (int i = 0; i <= CHB_ROWS / 2; ++i) {
+          const u16x2 r = __builtin_elementwise_min(f[i], f[CHB_ROWS - i].yx);
+          e[i * st] = r.x;
+          e[(CHB_ROWS - i) * st] = r.y;
+        }
       }
     }
-  }
-  __syncthreads();
-  // ---- along j + i = s, out to T ----
-  // Every row has a descriptor of its own that ends at the width: a store left or right of the row is dropped.
-  for (int d0 = 64 * wave; d0 < W + CHB_ROWS; d0 += CHB_NT) {
-    const int s = d0 + lane;
-    u16x2 f[CHB_ROWS + 1];
-    const bool none = empty(d0);
-    if (none) {
+    __syncthreads();
+  };
+  scan(E, P + 1);             // entry (i, d + i) of the guarded rows
+  scan(E + CHB_ROWS, P - 1);  // entry (i, s - i)
+  // ---- out: four columns a lane, a quarter of the wave's rows in flight ----
+  for (int c0 = 0; c0 < W; c0 += 256) {
+    const int j = c0 + 4 * lane;
+    const bool some = strips >> ((j >> 6) & 31) & 1u;
+    for (int i = wave; i < n; i += CHB_WAVES) {
+      if (j >= W) continue;
+      const u16x2* e = reinterpret_cast<const u16x2*>(E + i * P + CHB_ROWS + j);
+      u16x2 x = {0, 0}, y = {0, 0};
+      if (some) {
+        x = e[0];
+        y = e[1];
+      }
+      float* o = t + (int64_t)(r0 + i) * pitch + j;
+      const f32x4 T = {(float)x.x, (float)x.y, (float)y.x, (float)y.y};
+      if (j + 3 < W) {
+        __builtin_nontemporal_store(T, reinterpret_cast<f32x4*>(o));
+      } else {
 #pragma unroll
-      for (int i = 0; i <= CHB_ROWS; ++i) f[i] = u16x2{0, 0};
-    } else {
-      scan_both(E + CHB_ROWS + min(s, W + CHB_ROWS - 1), P - 1, B2, f);
-    }
-    float* tr = t + (int64_t)r0 * pitch;
-#pragma unroll
-    for (int i = 0; i < CHB_ROWS; ++i) {
-      const rsrc_t rr = make_rsrc(tr, i < n ? (uint32_t)W * 4u : 0u);
-      const uint32_t T = min((uint32_t)f[i].x, (uint32_t)f[CHB_ROWS - i].y);
-      // opaque, so that no part of it becomes the instruction's own offset: the sum of the two does not wrap
-      uint32_t off = (uint32_t)(s - i) * 4u;
-      asm("" : "+v"(off));
-      buf_stream((float)T, rr, off, 0);
-      tr += pitch;
+        for (int k = 0; k < 3; ++k)
+          if (j + k < W) __builtin_nontemporal_store(T[k], o + k);
+      }
     }
   }
 }
