@@ -301,12 +301,14 @@ __global__ void __launch_bounds__(CH_ROWS_NT) chamfer_rows_batched_kernel(const 
 //     path with steps along both diagonals is a path too.) Outside the lattice E
 //     is 0. The row stride of E is an odd number of words, so that 32 lanes on
 //     32 rows meet 32 banks.
+// Strips of 64 columns without foreground in a band skip the bit words and the
+// scans, and are filled with zeros only where a neighbour's scan reads them.
 // Traffic: the image and T once and 3/32 words per pixel of edges, 5.4 B/px.
-// Measured on 1,400 silhouettes (355 Mpx): 0.62 ms (edges 0.12, seams 0.07, bands
-// 0.43) against 2.42 ms of the column and row passes (0.34 + 2.10). T goes out
-// in non-temporal stores: ordinary ones took 0.52 ms in the bands and 0.04 ms
-// in the next call's edges, whose reads evict them; without stores the bands take
-// 0.37 ms, issue bound (bit words to E 0.21, the diagonals 0.16).
+// Measured on 1,400 silhouettes (355 Mpx, 23 % of the strips with foreground):
+// 0.58 ms (edges 0.12, seams 0.07, bands 0.39) against 2.42 ms of the column and
+// row passes (0.34 + 2.10). T goes out in non-temporal 16-byte stores: ordinary
+// ones cost the bands 0.09 ms and the next call's edges, whose reads evict
+// them, 0.04; written along the second scan's diagonals they cost 0.02.
 // ---------------------------------------------------------------------------
 constexpr int CHB_ROWS = 32;
 constexpr int CHB_NT = 512;
@@ -483,16 +485,18 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
     uint32_t top = 0u, bot = 0u;  // T | up of the first row, T | down of the seam below
     if (col && !first) top = t_word(t, pitch, r0)[j];
     if (col && !last) bot = t_word(t, pitch, r0 + CHB_ROWS - 1)[j];
-    for_each_index(
-        [&](auto kk) {
-          constexpr int k = decltype(kk)::value;
-          const uint64_t row = __ballot((m & (1u << k)) != 0u);
-          lo = (uint32_t)itc_writelane((int)(uint32_t)row, k, (int)lo);  // lane k keeps row k's words
-          hi = (uint32_t)itc_writelane((int)(uint32_t)(row >> 32), k, (int)hi);
-        },
-        std::make_integer_sequence<int, 32>{});
     const bool some_fg = __any(m != 0u);  // uniform
-    if (some_fg && lane == 0) atomicOr(fg, 1u << st);
+    if (some_fg) {
+      for_each_index(
+          [&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            const uint64_t row = __ballot((m & (1u << k)) != 0u);
+            lo = (uint32_t)itc_writelane((int)(uint32_t)row, k, (int)lo);  // lane k keeps row k's words
+            hi = (uint32_t)itc_writelane((int)(uint32_t)(row >> 32), k, (int)hi);
+          },
+          std::make_integer_sequence<int, 32>{});
+      if (lane == 0) atomicOr(fg, 1u << st);
+    }
     if (lane < CHB_ROWS) {
       F[lane * FS + 2 * st] = lo;
       F[lane * FS + 2 * st + 1] = hi;
@@ -501,11 +505,7 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
     }
     uint16_t* e = E + CHB_ROWS + j;
     e[CHB_ROWS * P] = (uint16_t)(bot & 0xffffu);  // 0 below the lattice
-    if (!some_fg) {
-#pragma unroll
-      for (int k = 0; k < CHB_ROWS; ++k) e[k * P] = 0;
-      continue;
-    }
+    if (!some_fg) continue;  // its zeros follow below, where a scan reads them
     // distances in units of a: up from the first row's, down from the seam below
     uint32_t dn[CHB_ROWS], run = (uint32_t)a * (bot >> 16);
 #pragma unroll
@@ -526,8 +526,14 @@ __device__ __forceinline__ void chamfer_band(const uint8_t* __restrict__ x, int6
   const uint32_t strips = *fg;  // strips with a foreground pixel
   // ---- E = min(E, a h): lane = (row, word of 32 columns), pairs of columns ----
   for (int st = wave; st < ns; st += CHB_WAVES) {
-    if (!(strips >> st & 1u)) continue;
     const int r = lane & 31, w = 2 * st + (lane >> 5);
+    if (!(strips >> st & 1u)) {
+      if ((((uint64_t)strips << 1 | strips >> 1) >> st & 1u) == 0) continue;  // nor has a neighbour foreground
+#pragma unroll
+      for (int k = 0; k < CHB_ROWS; k += 2)
+        *reinterpret_cast<u16x2*>(E + (k + (lane >> 5)) * P + CHB_ROWS + 64 * st + 2 * r) = u16x2{0, 0};
+      continue;
+    }
     const uint32_t m = F[r * FS + w];
     const uint64_t sr = S[r];
     const uint64_t before = sr & ((1ull << w) - 1ull);
