@@ -13,10 +13,13 @@
 // ring; M = -sigma^2 grad A by central differences (exact for a Gaussian
 // kernel: sum_y h(y) (x - y) g(x - y) = -sigma^2 d/dx sum_y h(y) g(x - y)).
 //
-// Both passes run down columns (lanes along columns, coalesced rows), so the
-// image is first transposed into an FP64 buffer E1 (rows = v), filtered,
-// transposed into E2 (rows = u), filtered, and the maps and S_X partials are
-// read off E2. The recursions run in FP64, segment-parallel along the lines.
+// The recursions run in FP64, segment-parallel along the lines, in two forms.
+// Lines of up to 64 x 39 samples along v and as many as the column workgroups
+// hold along u (RR_SEG, RC_SEG below) stay in registers, a segment a lane: two
+// kernels (second half of this file). Longer lines run down the columns of FP64
+// buffers (lanes along columns, coalesced rows): the image is transposed into
+// E1 (rows = v), filtered, transposed into E2 (rows = u), filtered, and the maps
+// and S_X partials are read off E2.
 #include "itc_device.h"
 
 namespace itc {
