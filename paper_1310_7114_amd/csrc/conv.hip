@@ -376,6 +376,29 @@ __global__ void __launch_bounds__(256) sx_total_kernel(ImageDesc im, const char*
   if (threadIdx.x == 0) *s_x = s;
 }
 
+// Reads the bytes of one list entry a workgroup (img 16-byte units from byte
+// 16 s0 of the weights) into the caches.
+__global__ void __launch_bounds__(256) read_ahead_kernel(const ConvTile* __restrict__ pieces, const char* wbase) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  constexpr int U = 8, NT = 256;
+  const ConvTile t = pieces[blockIdx.x];
+  const uintptr_t first = (uintptr_t)wbase + (uintptr_t)t.s0 * 16, up = (first + 15) / 16 * 16;
+  const u4* p = reinterpret_cast<const u4*>(up);
+  const int n = t.img - (up != first ? 1 : 0);
+  int i = threadIdx.x;
+  for (; i + (U - 1) * NT < n; i += U * NT) {
+    u4 v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = p[i + k * NT];
+#pragma unroll
+    for (int k = 0; k < U; ++k) asm volatile("" ::"v"(v[k]));
+  }
+  for (; i < n; i += NT) {
+    const u4 v = p[i];
+    asm volatile("" ::"v"(v));
+  }
+}
+
 // ---------------------------------------------------------------------------
 // host-side launch helpers
 // ---------------------------------------------------------------------------
@@ -407,6 +430,11 @@ hipError_t launch_conv_image(bool f64, const ImageDesc& im, const void* w, void*
     return hipGetLastError();
   switch (im.rclass) { ITC_FOR_CLASSES_F64(ITC_CASE) default: return hipErrorInvalidValue; }
 #undef ITC_CASE
+}
+
+hipError_t launch_read_ahead(const ConvTile* d_pieces, const void* w, int pieces, hipStream_t s) {
+  hipLaunchKernelGGL(read_ahead_kernel, dim3(pieces), dim3(256), 0, s, d_pieces, (const char*)w);
+  return hipGetLastError();
 }
 
 hipError_t launch_sx_finalize(const ImageDesc& img, const void* maps, double* s_x, hipStream_t s) {

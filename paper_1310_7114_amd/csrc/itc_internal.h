@@ -138,6 +138,8 @@ int conv_f32_blocks_per_cu(int rclass);
 // the stream.
 hipError_t count_nonfinite_weights(const ImageDesc* h_image, const ImageDesc* d_images, int n, const void* w,
                                    unsigned int* count, hipStream_t s);
+// Reads weights into the caches: `pieces` list entries (img 16-byte units from byte 16 s0).
+hipError_t launch_read_ahead(const ConvTile* d_pieces, const void* weights, int pieces, hipStream_t s);
 // S_X of one image: the fixed-order sum of its FP64 partials.
 hipError_t launch_sx_finalize(const ImageDesc& img, const void* maps, double* s_x, hipStream_t s);
 // 3-D lattices: one volume (slice, row, column) and its window radius.

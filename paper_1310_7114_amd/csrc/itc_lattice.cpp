@@ -203,8 +203,9 @@ struct itc_plan {
   int max_passes = 1;  // largest fit pass count over the images
   std::vector<ImageDesc> images;
   // convolution class keys of the plan (tile shapes are set per key) and its
-  // launches: one per FP32 class, one for every matrix-core class
-  // together; launch l covers tiles [launch_begin[l], launch_end[l])
+  // launches: one per FP32 class, one for every 8-bit class together or, with
+  // weights that are read ahead in groups, two a group; launch l covers tiles
+  // [launch_begin[l], launch_end[l])
   std::vector<ConvTile> tiles;
   std::vector<int> cls;
   std::vector<int> launch_key, launch_begin, launch_end, launch_grid;
@@ -213,6 +214,7 @@ struct itc_plan {
   // convolution tile shape per class key (set by the autotuning hook; 0 =
   // default): target segment rows and workgroups per compute unit
   std::vector<int> key_seg, key_per;
+  int conv_launches = 0;  // classes with a launch of their own
   size_t tile_cap = 0;  // capacity of d_tiles (the most tiles any shape gives)
   // fit schedule: workgroup g of the fit launch (fit_grid workgroups) takes
   // the images fit_list[fit_begin[g] .. fit_begin[g + 1]) in turn
@@ -247,6 +249,7 @@ struct itc_plan {
 // overlap) goes whole to the XCD with the least cost so far, so the
 // overlapping input lines are read into one L2.
 constexpr int PLAN_NKEYS = itc::CONV_MX_CLASS + 33;
+constexpr int CONV_READ = -1;  // launch key: read the weights of the group that follows
 constexpr int PLAN_SEG_DEFAULT = 256, PLAN_SEG_MIN = 64, PLAN_SEG_MAX = 4096;
 
 // Fit schedule: the images, most expensive first, dealt to the F x C
@@ -291,6 +294,47 @@ static int class_occupancy(const itc_plan* p, int key) {
   return per < 1 ? 1 : per;
 }
 
+// Reading ahead. HBM loses time to every change between reads and writes: beside
+// the map stores the weights of the 8-bit convolution, which the stores bound,
+// cost three times what they do alone, unless the memory-side cache (256 MB) has
+// them. Weights that do not fit it are read in groups of half its size, in a
+// launch of reads only before the group's tiles, which then find them there.
+// 1,400 silhouettes (360 MB): 1.15 -> 1.09 ms; 400 x 1024^2 bytes 1.30 -> 1.25; at
+// 256 MB 0.79 either way; groups of 64 MB 1.11, of 192 MB 1.15. The FP32 classes
+// lose by it (64 x 1024^2 weights, 256 MB: 0.29 -> 0.31 ms): they share their
+// bound with the matrix unit.
+constexpr int64_t READ_AHEAD_MIN = 256ll << 20, READ_AHEAD_GROUP = 128ll << 20;
+
+static int64_t weight_bytes(const ImageDesc& im) {
+  const int64_t esz = im.wdtype == 0 ? 1 : (im.wdtype == 1 ? 4 : 8);
+  return ((int64_t)(im.H - 1) * im.pitch + im.W) * esz;
+}
+
+static int plan_read_groups(int64_t bytes) {
+  return bytes > READ_AHEAD_MIN ? (int)((bytes + READ_AHEAD_GROUP - 1) / READ_AHEAD_GROUP) : 1;
+}
+
+// About `pieces` list entries of equal size (img 16-byte units from byte 16 s0 of the weights) that cover the ranges.
+// Gaps below a page are read as well: each of their bytes shares a page with a weight.
+static std::vector<ConvTile> read_pieces(std::vector<std::pair<int64_t, int64_t>>& ranges, int pieces) {
+  std::sort(ranges.begin(), ranges.end());
+  std::vector<std::pair<int64_t, int64_t>> merged;
+  int64_t total = 0;
+  for (const auto& r : ranges) {
+    if (!merged.empty() && r.first < merged.back().second + 4096)
+      merged.back().second = std::max(merged.back().second, r.second);
+    else
+      merged.push_back(r);
+  }
+  for (const auto& r : merged) total += r.second - r.first;
+  std::vector<ConvTile> out;
+  const int64_t piece = (total / pieces + 16) / 16 * 16;
+  for (const auto& r : merged)
+    for (int64_t a = (r.first + 15) / 16 * 16; a + 16 <= r.second; a += piece)
+      if (a / 16 <= INT32_MAX) out.push_back(ConvTile{(int32_t)(std::min(piece, r.second - a) / 16), 0, (int32_t)(a / 16), 0});
+  return out;
+}
+
 static void build_conv_tiles(itc_plan* p) {
   std::vector<std::vector<ConvTile>> by_class(PLAN_NKEYS);
   std::vector<std::vector<int64_t>> cost_of(PLAN_NKEYS);
@@ -317,68 +361,94 @@ static void build_conv_tiles(itc_plan* p) {
   p->launch_end.clear();
   p->launch_grid.clear();
   p->launch_split.clear();
+  p->conv_launches = 0;
+  for (int key = 0; key < PLAN_NKEYS; ++key)
+    if (!by_class[key].empty()) p->cls.push_back(key);
   const int cus = device_cus();
-  auto append_sorted = [&](int key) {
-    std::vector<int> idx(by_class[key].size());
-    std::iota(idx.begin(), idx.end(), 0);
-    std::stable_sort(idx.begin(), idx.end(), [&](int a, int c) { return cost_of[key][a] > cost_of[key][c]; });
-    for (int k : idx) p->tiles.push_back(by_class[key][k]);
-  };
-  // deal the segment rows of tiles [begin, end) (runs of tiles of one image
-  // and segment, adjacent after the sort) to the XCD sublists, least loaded first
-  auto deal_xcd = [&](int begin) {
-    std::vector<std::vector<ConvTile>> sub(itc::CONV_XCDS);
-    std::vector<int64_t> load(itc::CONV_XCDS, 0);
-    for (int a = begin; a < (int)p->tiles.size();) {
-      int b = a;
-      int64_t cost = 0;
-      while (b < (int)p->tiles.size() && p->tiles[b].img == p->tiles[a].img && p->tiles[b].s0 == p->tiles[a].s0) {
-        const ImageDesc& im = p->images[p->tiles[b].img];
-        const int halo = class_key_of(im) >= itc::CONV_MX_CLASS ? itc::conv_mx_radius(im.rclass) : im.rclass;
-        cost += std::min(p->tiles[b].S, im.H - p->tiles[b].s0) + 2 * halo;
-        ++b;
-      }
-      const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-      sub[x].insert(sub[x].end(), p->tiles.begin() + a, p->tiles.begin() + b);
-      load[x] += cost;
-      a = b;
-    }
-    p->tiles.resize(begin);
-    itc::XcdSplit xs{};
-    for (int x = 0; x < itc::CONV_XCDS; ++x) {
-      xs.beg[x] = (int)p->tiles.size() - begin;
-      p->tiles.insert(p->tiles.end(), sub[x].begin(), sub[x].end());
-    }
-    xs.beg[itc::CONV_XCDS] = (int)p->tiles.size() - begin;
-    return xs;
-  };
-  auto add_launch = [&](int key, int begin, int per) {
-    const itc::XcdSplit xs = deal_xcd(begin);
+  auto launch = [&](int key, int begin, int grid, const itc::XcdSplit& xs) {
     p->launch_key.push_back(key);
     p->launch_begin.push_back(begin);
     p->launch_end.push_back((int)p->tiles.size());
-    // no more workgroups than tiles (rounded to whole XCD rounds), at most `per` per compute unit
-    const int ntiles = (int)p->tiles.size() - begin;
-    const int grid = std::min(per * cus, (ntiles + itc::CONV_XCDS - 1) / itc::CONV_XCDS * itc::CONV_XCDS);
-    p->launch_grid.push_back(std::max(itc::CONV_XCDS, grid / itc::CONV_XCDS * itc::CONV_XCDS));
+    p->launch_grid.push_back(grid);
     p->launch_split.push_back(xs);
   };
-  for (int key = 0; key < PLAN_NKEYS; ++key)
-    if (!by_class[key].empty()) p->cls.push_back(key);
-  for (int key = 0; key < itc::CONV_MX_CLASS; ++key) {
-    if (by_class[key].empty()) continue;
-    const int begin = (int)p->tiles.size();
-    append_sorted(key);
-    add_launch(key, begin, p->key_per[key] > 0 ? p->key_per[key] : class_occupancy(p, key));
-  }
-  const int begin = (int)p->tiles.size();
+  // The tiles of the classes `keys`, in that order: one launch, or one a group with the group's weights read before.
+  auto add_launch = [&](int launch_key, const std::vector<int>& keys, int per) {
+    ++p->conv_launches;
+    std::vector<char> used(p->n, 0);
+    for (int key : keys)
+      for (const ConvTile& t : by_class[key]) used[t.img] = 1;
+    int64_t total = 0;
+    for (int i = 0; i < p->n; ++i)
+      if (used[i]) total += weight_bytes(p->images[i]);
+    const int ngroups = launch_key >= itc::CONV_MX_CLASS ? plan_read_groups(total) : 1;
+    std::vector<int> group(p->n, 0);
+    int64_t before = 0;
+    for (int i = 0; i < p->n; ++i) {
+      group[i] = (int)std::min<int64_t>(ngroups - 1, before * ngroups / std::max<int64_t>(1, total));
+      if (used[i]) before += weight_bytes(p->images[i]);
+    }
+    for (int g = 0; g < ngroups; ++g) {
+      int begin = (int)p->tiles.size();
+      if (ngroups > 1) {
+        std::vector<std::pair<int64_t, int64_t>> ranges;  // byte ranges of the group's weights
+        for (int i = 0; i < p->n; ++i)
+          if (used[i] && group[i] == g)
+            ranges.push_back({p->images[i].weight_off, p->images[i].weight_off + weight_bytes(p->images[i])});
+        const std::vector<ConvTile> ahead = read_pieces(ranges, 4 * cus);
+        p->tiles.insert(p->tiles.end(), ahead.begin(), ahead.end());
+        if (!ahead.empty()) launch(CONV_READ, begin, (int)ahead.size(), itc::XcdSplit{});
+        begin = (int)p->tiles.size();
+      }
+      std::vector<std::vector<ConvTile>> sub(itc::CONV_XCDS);
+      std::vector<int64_t> load(itc::CONV_XCDS, 0);
+      for (int key : keys) {
+        const std::vector<ConvTile>& tiles = by_class[key];
+        const std::vector<int64_t>& cost = cost_of[key];
+        std::vector<int> idx;
+        for (int k = 0; k < (int)tiles.size(); ++k)
+          if (group[tiles[k].img] == g) idx.push_back(k);
+        std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+        // deal the segment rows (runs of tiles of one image and segment, adjacent after the sort) to the XCD
+        // sublists, least loaded first
+        for (size_t u = 0; u < idx.size();) {
+          size_t v = u;
+          int64_t c = 0;
+          while (v < idx.size() && tiles[idx[v]].img == tiles[idx[u]].img && tiles[idx[v]].s0 == tiles[idx[u]].s0) {
+            const ConvTile& t = tiles[idx[v]];
+            const ImageDesc& im = p->images[t.img];
+            const int halo = key >= itc::CONV_MX_CLASS ? itc::conv_mx_radius(im.rclass) : im.rclass;
+            c += std::min(t.S, im.H - t.s0) + 2 * halo;
+            ++v;
+          }
+          const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+          for (; u < v; ++u) sub[x].push_back(tiles[idx[u]]);
+          load[x] += c;
+        }
+      }
+      itc::XcdSplit xs{};
+      for (int x = 0; x < itc::CONV_XCDS; ++x) {
+        xs.beg[x] = (int)p->tiles.size() - begin;
+        p->tiles.insert(p->tiles.end(), sub[x].begin(), sub[x].end());
+      }
+      const int ntiles = (int)p->tiles.size() - begin;
+      xs.beg[itc::CONV_XCDS] = ntiles;
+      if (ntiles == 0) continue;
+      // no more workgroups than tiles (rounded to whole XCD rounds), at most `per` per compute unit
+      const int grid = std::min(per * cus, (ntiles + itc::CONV_XCDS - 1) / itc::CONV_XCDS * itc::CONV_XCDS);
+      launch(launch_key, begin, std::max(itc::CONV_XCDS, grid / itc::CONV_XCDS * itc::CONV_XCDS), xs);
+    }
+  };
+  for (int key = 0; key < itc::CONV_MX_CLASS; ++key)
+    if (!by_class[key].empty()) add_launch(key, {key}, p->key_per[key] > 0 ? p->key_per[key] : class_occupancy(p, key));
+  std::vector<int> keys;
   int per = class_occupancy(p, itc::CONV_MX_CLASS);
   for (int key = PLAN_NKEYS - 1; key >= itc::CONV_MX_CLASS; --key) {
     if (by_class[key].empty()) continue;
-    append_sorted(key);
+    keys.push_back(key);
     if (p->key_per[key] > 0) per = std::min(per, p->key_per[key]);
   }
-  if ((int)p->tiles.size() > begin) add_launch(itc::CONV_MX_CLASS + p->mx_max_ra, begin, per);
+  if (!keys.empty()) add_launch(itc::CONV_MX_CLASS + p->mx_max_ra, keys, per);
 }
 
 extern "C" {
@@ -625,6 +695,13 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
   p->key_per.assign(PLAN_NKEYS, 0);
   for (const ImageDesc& im : p->images)
     if (class_key_of(im) >= itc::CONV_MX_CLASS) p->mx_max_ra = std::max(p->mx_max_ra, itc::conv_mx_radius(im.rclass));
+  {
+    int64_t bytes = 0;
+    for (const ImageDesc& im : p->images) bytes += weight_bytes(im);
+    // pieces read ahead: four a compute unit and group, and two a gap between images
+    if (plan_read_groups(bytes) > 1)
+      p->tile_cap += (size_t)(bytes / READ_AHEAD_GROUP + 1) * 4 * (size_t)device_cus() + 2 * (size_t)p->n;
+  }
   build_conv_tiles(p);
   const int cus = device_cus();
   int fper = itc::fit_blocks_per_cu(false, p->m_max, p->max_passes);
@@ -672,7 +749,7 @@ int32_t itc_lattice_plan_size(const itc_plan* p) { return p ? p->n : -1; }
 
 int32_t itc_lattice_plan_conv_classes(const itc_plan* p) { return p ? (int32_t)p->cls.size() : -1; }
 
-int32_t itc_lattice_plan_conv_launches(const itc_plan* p) { return p ? (int32_t)p->launch_key.size() : -1; }
+int32_t itc_lattice_plan_conv_launches(const itc_plan* p) { return p ? p->conv_launches : -1; }
 
 itc_status itc_lattice_plan_conv_class(const itc_plan* p, int32_t c, int32_t* key, int32_t* seg_rows,
                                        int32_t* blocks_per_cu, int32_t* max_blocks_per_cu) {
@@ -768,7 +845,9 @@ itc_status itc_lattice_precompute_batched(itc_plan* p, const void* weights, void
   for (size_t l = 0; l < p->launch_key.size(); ++l) {
     const int key = p->launch_key[l];
     hipError_t e =
-        key >= itc::CONV_MX_CLASS
+        key == CONV_READ
+            ? itc::launch_read_ahead(p->d_tiles + p->launch_begin[l], weights, p->launch_grid[l], (hipStream_t)stream)
+        : key >= itc::CONV_MX_CLASS
             ? itc::launch_conv_mx_tiles(key - itc::CONV_MX_CLASS, p->d_images, p->d_tiles + p->launch_begin[l],
                                         p->launch_split[l], weights, maps, p->launch_grid[l], (hipStream_t)stream)
             : itc::launch_conv_f32_tiles(key, p->d_images, p->d_tiles + p->launch_begin[l], p->launch_split[l],
