@@ -381,7 +381,7 @@ def gpu_extras(dev, cases, itc, synth):
 
     # differentiation: forward D and the adjoint (dD/dw, dD/dh) of 64 weighted
     # 1024 x 1024 images, M = 256, sigma = 4, FP32 per-pixel weights h = g/255
-    # (the autograd path: FP32 weights take the vector-ALU convolution)
+    # (the autograd path: FP32 weights take the FP32 matrix-core convolution)
     c5 = synth.config5_cases(64)
     B5, H5, W5, M5 = len(c5), 1024, 1024, 256
     p5 = itc.BatchPlan.for_stack(B5, H5, W5, M5, 4.0, iters=0, dtype=torch.float32, device=dev)
@@ -510,8 +510,8 @@ def main():
     done = torch.empty(n, dtype=torch.int32, device=dev)
 
     # ---------------- batched step: two HIP graphs (convolution, fit + D) ----------------
-    # The convolution of an 8-bit batch is one persistent kernel launch and the
-    # fit another; each is captured in a graph of its own, and HIP events
+    # The convolution of an 8-bit batch is a persistent launch per group of weights
+    # and the fit one launch; each is captured in a graph of its own, and HIP events
     # recorded between the replays (on the replay stream) time every launch of
     # the timed steps.
     conv_fn = plan.precompute

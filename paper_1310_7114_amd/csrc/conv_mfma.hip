@@ -1,7 +1,7 @@
 // Separable Gaussian convolution maps on the matrix cores, for 8-bit lattice
 // weights and FP32 maps (Section 3.1: the Parzen sum of delta impulses is the
 // weight image convolved with a Gaussian, whose mask factorises into 1-D
-// masks). The maps are the same as the VALU kernel's:
+// masks). The maps:
 //   A = (I *_v g) *_u g,   M_u = (I *_v g) *_u tg,   M_v = (I *_v tg) *_u g,
 // with f(t) the tap at t = x_out - x_in, plus the FP64 partials of S_X.
 //

@@ -228,7 +228,14 @@ template <typename P>
 __device__ inline double block_sum_fixed(const P* p, int64_t n, double* red) {
   const int nt = blockDim.x, tid = threadIdx.x;
   double s = 0.0;
-  for (int64_t i = tid; i < n; i += nt) s += (double)p[i];
+  constexpr int U = 8;  // loads in flight; the additions keep their order
+  for (int64_t i = tid; i < n; i += (int64_t)U * nt) {
+    P v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = p[i + k * nt < n ? i + k * nt : n - 1];
+#pragma unroll
+    for (int k = 0; k < U; ++k) s += i + k * nt < n ? (double)v[k] : 0.0;
+  }
   return block_reduce_fixed(s, red);
 }
 
