@@ -424,7 +424,7 @@ __device__ __forceinline__ void chamfer_seam(float* __restrict__ t, int64_t pitc
   for (int j = threadIdx.x; j < W; j += blockDim.x) {
     const uint32_t e = row[j];  // this thread alone rewrites it
     const uint32_t T = (uint32_t)row_search(gs, j, W, a, b - a);
-    row[j] = T | e << 16;               // T | up
+    if (e != 0u) row[j] = T | e << 16;  // T | up (a background pixel's word is 0 already)
     above[j] = T | (e & 0xffff0000u);  // T | down
   }
 }
