@@ -62,22 +62,28 @@ __device__ __forceinline__ double weight_at(const WT* x, const VolumeGeom& vg, i
 // In-plane passes of one tile: Q00, Q01, Q10 for rows [u0, u0 + 32) and
 // columns [v0, v0 + 64) of slice s (blockIdx = (column tile, row tile, s)).
 // SROWS >= (32 + 2R) / 4 rows of the staged tile per wave (12, 16 or 24).
+// 96 x 192 x 256 voxels, R = 6: 25 us (staging 8, v pass 6, u pass 6, stores 4); with an
+// LDS read for every tap and row the v pass took 9 (R = 24: all maps 168 us, now 138).
 template <typename WT, int SROWS>
 __global__ void __launch_bounds__(VOL_NT) vol_plane_kernel(const WT* __restrict__ x, VolumeGeom vg, VolTaps tp,
                                                            float* __restrict__ q00, float* __restrict__ q01,
                                                            float* __restrict__ q10) {
-  extern __shared__ float X[];  // [4 SROWS][RP]: weights of rows u0 - R.., columns v0 - R.., then P0 | P1
-  const int R = vg.R, XW = 64 + 2 * R, RP = XW > 128 ? XW : 128;
+  // [4 SROWS][RP]: weights of rows u0 - R.., columns v0 - R.. (64 + 2 R <= RP of them), then P0 | P1
+  extern __shared__ __align__(16) float X[];
+  constexpr int RP = 128, NS = SROWS / 4;
+  static_assert(64 + 2 * VOL_MAXR <= RP && SROWS % 4 == 0, "a staged row; four rows a step of the v pass");
+  const int R = vg.R, XW = 64 + 2 * R;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int v0 = blockIdx.x * 64, u0 = blockIdx.y * VOL_TR, s = blockIdx.z;
-  // staging: wave wv takes rows wv, wv + 4, ... (SROWS of them, at most 2
+  // staging: wave wv takes rows 16 m + 4 wv .. + 3 (SROWS of them, at most 2
   // columns per lane) and issues all their loads before the first is used;
   // positions off the lattice load a clamped position and store 0
   const WT* xs = x + (int64_t)s * vg.slice_pitch;
+  auto staged_row = [&](int q) { return 16 * (q >> 2) + 4 * wv + (q & 3); };
   WT raw[SROWS][2];
 #pragma unroll
   for (int q = 0; q < SROWS; ++q) {
-    const int u = min(max(u0 - R + wv + q * (VOL_NT / 64), 0), vg.H - 1);
+    const int u = min(max(u0 - R + staged_row(q), 0), vg.H - 1);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int v = min(max(v0 - R + lane + 64 * h, 0), vg.W - 1);
@@ -86,7 +92,7 @@ __global__ void __launch_bounds__(VOL_NT) vol_plane_kernel(const WT* __restrict_
   }
 #pragma unroll
   for (int q = 0; q < SROWS; ++q) {
-    const int j = wv + q * (VOL_NT / 64), u = u0 - R + j;
+    const int j = staged_row(q), u = u0 - R + j;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int c = lane + 64 * h, v = v0 - R + c;
@@ -94,27 +100,52 @@ __global__ void __launch_bounds__(VOL_NT) vol_plane_kernel(const WT* __restrict_
       if (c < XW) X[j * RP + c] = on ? (float)(vg.scale * (double)raw[q][h]) : 0.f;
     }
   }
-  // v pass, taps outermost (each tap is fetched once per wave): output column
-  // lane of each of the wave's rows reads columns lane + R - t of that row,
-  // which no other wave touches, so P0 | P1 overwrite the rows in place
+  // v pass, taps outermost (each tap is fetched once per wave): lane (r, c) makes columns 4c .. 4c + 3 of the
+  // wave's rows 16 m + 4 wv + r from a window of registers that takes four more columns, one LDS read, every
+  // four taps. No other wave touches the rows, so P0 | P1 overwrite them in place.
   {
-    float a0[SROWS], a1[SROWS];
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    float* xr = X + (4 * wv + (lane >> 4)) * RP + 4 * (lane & 15);
+    f4 w[NS], a0[NS], a1[NS];
 #pragma unroll
-    for (int q = 0; q < SROWS; ++q) a0[q] = a1[q] = 0.f;
-    const float* xr = X + wv * RP + lane + R;
-    for (int t = -R; t <= R; ++t) {
-      const float g = tp.g[t + R + VOL_RUN - 1], tg = tp.tg[t + R + VOL_RUN - 1];
-#pragma unroll
-      for (int q = 0; q < SROWS; ++q) {
-        const float h = xr[q * (VOL_NT / 64) * RP - t];
-        a0[q] = fmaf(g, h, a0[q]);
-        a1[q] = fmaf(tg, h, a1[q]);
-      }
+    for (int m = 0; m < NS; ++m) {
+      w[m] = *reinterpret_cast<const f4*>(xr + 16 * m * RP);
+      a0[m] = a1[m] = f4{0.f, 0.f, 0.f, 0.f};
     }
+    // taps R - u - e for e < n: output i takes window column i + e
+    auto taps = [&](int u, auto N) __attribute__((always_inline)) {
+      constexpr int n = decltype(N)::value;
+      float g[n], tg[n];
 #pragma unroll
-    for (int q = 0; q < SROWS; ++q) {
-      X[(wv + q * (VOL_NT / 64)) * RP + lane] = a0[q];
-      X[(wv + q * (VOL_NT / 64)) * RP + 64 + lane] = a1[q];
+      for (int e = 0; e < n; ++e) {
+        g[e] = tp.g[2 * R - u - e + VOL_RUN - 1];
+        tg[e] = tp.tg[2 * R - u - e + VOL_RUN - 1];
+      }
+#pragma unroll
+      for (int m = 0; m < NS; ++m) {
+        f4 nx = w[m];
+        if constexpr (n > 1) nx = *reinterpret_cast<const f4*>(xr + 16 * m * RP + u + 4);
+#pragma unroll
+        for (int e = 0; e < n; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float h = i + e < 4 ? w[m][(i + e) & 3] : nx[(i + e) & 3];
+            a0[m][i] = fmaf(g[e], h, a0[m][i]);
+            a1[m][i] = fmaf(tg[e], h, a1[m][i]);
+          }
+        w[m] = nx;
+      }
+    };
+    int u = 0;
+    for (; u + 3 <= 2 * R; u += 4) taps(u, std::integral_constant<int, 4>{});
+    if (u == 2 * R)  // uniform: 2 R + 1 taps leave one or three
+      taps(u, std::integral_constant<int, 1>{});
+    else
+      taps(u, std::integral_constant<int, 3>{});
+#pragma unroll
+    for (int m = 0; m < NS; ++m) {
+      *reinterpret_cast<f4*>(xr + 16 * m * RP) = a0[m];
+      *reinterpret_cast<f4*>(xr + 16 * m * RP + 64) = a1[m];
     }
   }
   __syncthreads();
