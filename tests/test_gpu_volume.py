@@ -58,6 +58,21 @@ def test_volume_maps(gpu_lib, name, build, sigma, scale, radius, pad):
     assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
 
 
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 7, 8, 9, 16, 31, 32])
+def test_volume_maps_radii(gpu_lib, R):
+    """Radii that leave one or three taps of the in-plane window, at the compiled row counts' limits, on tiles
+    with ragged rows and columns and depths that end inside a thread's run."""
+    rng = np.random.default_rng(R)
+    for shape in [(1, 33, 65), (9, 31, 64), (17, 5, 130)]:
+        vol = rng.integers(0, 256, shape).astype(np.uint8)
+        _, got, sx = gpu_maps(gpu_lib, vol, R / 3.0, 1 / 255, R)
+        I = vol.astype(np.float64) / 255
+        ref = oracle_moments(O.volume_maps(I, R / 3.0, R))
+        for g, r in zip(got, ref):
+            assert normwise(g, r) <= 1e-5
+        assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
+
+
 def test_volume_fit(gpu_lib):
     case = S.volume_case(0)
     m, _, _ = gpu_maps(gpu_lib, case.vol, case.sigma)
