@@ -558,7 +558,13 @@ __global__ void __launch_bounds__(RecCols<COLS>::NT) rec_cols_kernel(const doubl
   asm("" : "+v"(o1));
   const rsrc_t xr = make_rsrc(x, (uint32_t)((uint64_t)H * (uint64_t)pitch * sizeof(WT)));
   const uint32_t xrow = (uint32_t)pitch * (uint32_t)sizeof(WT);
-  uint32_t xo = px ? (uint32_t)(n0 - 1) * xrow + (uint32_t)v * (uint32_t)sizeof(WT) : BUF_OOB;
+  // The weights of the line's rows, below 2^31 like xrow. Rows past the image stay at BUF_OOB: with a wide pitch
+  // their offsets would wrap back into the buffer.
+  auto weight_off = [&](int u) {
+    return px && (unsigned)u < (unsigned)H ? (uint32_t)u * xrow + (uint32_t)v * (uint32_t)sizeof(WT) : BUF_OOB;
+  };
+  const uint32_t x0 = weight_off(n0 - 1);
+  uint32_t xo = weight_off(n0);
   const double* eb = sm.edge[lane == 0 ? wave : wave + 2][lane == 0];  // lane 0: the wave before's last lane
   const double before = on ? sm.last[sg][c] : 0.0, after = on ? sm.first[sg + 1][c] : 0.0;
   double sx = 0.0;
@@ -569,8 +575,8 @@ __global__ void __launch_bounds__(RecCols<COLS>::NT) rec_cols_kernel(const doubl
         WT h[nb];
 #pragma unroll
         for (int q = 0; q < nb; ++q) {
-          h[q] = buf_load<WT>(xr, xo, 0);
-          xo = px ? xo + xrow : BUF_OOB;
+          h[q] = buf_load<WT>(xr, j0 + q == 0 ? x0 : xo, 0);
+          if (j0 + q > 0) xo = min(xo + xrow, BUF_OOB);
         }
 #pragma unroll
         for (int q = 0; q < nb; ++q) {

@@ -85,6 +85,23 @@ def test_recursive_pitch(gpu_lib):
         assert normwise(g, r) <= 1e-6
 
 
+@pytest.mark.parametrize("H,pitch,dt", [(60, 35_000_000, torch.uint8), (100, 5_000_000, torch.float32)])
+def test_recursive_wide_pitch(gpu_lib, H, pitch, dt):
+    """A cross-section of a large buffer: H + ceil(6 sigma) rows of the pitch pass 4 GiB, so a 32-bit row offset
+    past the image would come back inside the buffer, whose other columns are not zero."""
+    W, sigma = 70, 40.0
+    img = np.random.default_rng(H).uniform(size=(H, W)) * 255
+    img = img.astype(np.uint8) if dt == torch.uint8 else img.astype(np.float32)
+    buf = torch.full((H, pitch), 255, dtype=dt, device="cuda")
+    buf[:, :W] = torch.from_numpy(img).cuda()
+    m = gpu_lib.precompute_recursive(buf[:, :W], sigma, scale=0.5)
+    torch.cuda.synchronize()
+    A, Mu, Mv, sx_ref = O.recursive_maps(img.astype(np.float64) * 0.5, sigma)
+    for g, r in zip(m.planes(), (A, Mu, Mv)):
+        assert normwise(g.cpu().double().numpy(), r) <= 1e-6
+    assert float(m.s_x.cpu()[0]) == pytest.approx(sx_ref, rel=1e-6)
+
+
 def test_fit_on_recursive_maps(gpu_lib):
     """512 x 512 shapes, M = 100, sigma = 16 (beyond the masks' radius limit).
 
