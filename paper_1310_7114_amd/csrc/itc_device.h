@@ -162,6 +162,14 @@ __device__ __forceinline__ float wave_max_nonneg(float x) {
   return lane_value(x, 63);
 }
 
+// Orders a wave's accesses to LDS that its lanes exchange without a barrier: the
+// hardware keeps their order, and neither the optimiser (which may prove that one
+// lane's store and load do not meet) nor the scheduler moves one across.
+__device__ __forceinline__ void wave_lds_order() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // Buffer access: a uniform base in a resource descriptor, a per-lane 32-bit
 // byte offset and a uniform 32-bit byte offset (scalar register). The

@@ -366,7 +366,7 @@ __global__ void __launch_bounds__(64 * RR_ROWS) rec_rows_kernel(const WT* __rest
   }
 #pragma unroll
   for (int q = 0; q < SEG; ++q) buf[64 * q + lane] = factor * (double)raw[q];
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   double s[SEG], z[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int j = 0; j < SEG; ++j) s[j] = buf[lane * SEG + j];
@@ -378,10 +378,10 @@ __global__ void __launch_bounds__(64 * RR_ROWS) rec_rows_kernel(const WT* __rest
   seg_run<SEG, false, false>(rl, s, z);
   lane_scan<false>(rl, z, lane);
   seg_run<SEG, false, true>(rl, s, z);
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
 #pragma unroll
   for (int j = 0; j < SEG; ++j) buf[lane * SEG + j] = s[j];
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_order();
   // E1[run][u][C]: columns COLS run - 1 .. COLS run + COLS of the image
   constexpr int C = RecCols<COLS>::C;
   const int n = (W + COLS - 1) / COLS * C;

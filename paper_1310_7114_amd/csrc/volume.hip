@@ -100,6 +100,7 @@ __global__ void __launch_bounds__(VOL_NT) vol_plane_kernel(const WT* __restrict_
       if (c < XW) X[j * RP + c] = on ? (float)(vg.scale * (double)raw[q][h]) : 0.f;
     }
   }
+  wave_lds_order();
   // v pass, taps outermost (each tap is fetched once per wave): lane (r, c) makes columns 4c .. 4c + 3 of the
   // wave's rows 16 m + 4 wv + r from a window of registers that takes four more columns, one LDS read, every
   // four taps. No other wave touches the rows, so P0 | P1 overwrite them in place.
@@ -142,6 +143,7 @@ __global__ void __launch_bounds__(VOL_NT) vol_plane_kernel(const WT* __restrict_
       taps(u, std::integral_constant<int, 1>{});
     else
       taps(u, std::integral_constant<int, 3>{});
+    wave_lds_order();
 #pragma unroll
     for (int m = 0; m < NS; ++m) {
       *reinterpret_cast<f4*>(xr + 16 * m * RP) = a0[m];

@@ -73,6 +73,21 @@ def test_volume_maps_radii(gpu_lib, R):
         assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
 
 
+@pytest.mark.parametrize("R", [8, 16, 32])
+def test_volume_maps_in_plane_handoff(gpu_lib, R):
+    """The in-plane pass reads columns that other lanes of its wave staged and overwrites them in place: a window of
+    the widest radius of each compiled row count over a full tile of voxels that all differ. One slice, so the depth
+    pass adds nothing, and S_X sees every column."""
+    H, W = 32, 64 + 2 * R
+    vol = np.random.default_rng(100 + R).permutation(H * W).reshape(1, H, W).astype(np.float32)
+    _, got, sx = gpu_maps(gpu_lib, vol, R / 3.0, 1.0 / (H * W), R)
+    I = vol.astype(np.float64) / (H * W)
+    ref = oracle_moments(O.volume_maps(I, R / 3.0, R))
+    for g, r in zip(got, ref):
+        assert np.abs(g - r).max() <= 1e-5 * max(np.abs(r).max(), 1e-300)
+    assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
+
+
 def test_volume_fit(gpu_lib):
     case = S.volume_case(0)
     m, _, _ = gpu_maps(gpu_lib, case.vol, case.sigma)
