@@ -647,7 +647,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": conv_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": conv_gbs / HBM_PEAK_GBS,
                      "traffic": conv_prof["traffic_bytes_per_step"] if conv_prof else None,
-                     "kernel": "conv_mx_tiles_kernel (persistent; weights above 256 MiB in groups read ahead, counted as one launch)",
+                     "kernel": "conv_mx_tiles_kernel (persistent; weights above 256 MiB in groups, each read ahead by a launch of its own)",
                      "launches_per_step": conv_launches, "bytes_per_px": CONV_BYTES_PER_PX,
                      "algorithmic_bytes": conv_bytes, "ms": conv_s * 1e3,
                      "direct_form_tflops": conv_tfs},

@@ -488,9 +488,9 @@ int32_t itc_lattice_plan_size(const itc_plan* p);
  *   shapes, so capture after tuning.
  */
 int32_t itc_lattice_plan_conv_classes(const itc_plan* p);
-/* Kernel launches of the plan's convolution (one per FP32 class, one for all
- * classes of aligned 8-bit rows together, which 8-bit weights above 256 MiB
- * divide into groups of at most 128 MiB, counted once); -1 if p is NULL. */
+/* Kernel launches of the plan's convolution: one per FP32 class, and one for all
+ * classes of aligned 8-bit rows together, or two a group of their images where
+ * 8-bit weights above 256 MiB are read ahead in groups; -1 if p is NULL. */
 int32_t itc_lattice_plan_conv_launches(const itc_plan* p);
 itc_status itc_lattice_plan_conv_class(const itc_plan* p, int32_t c, int32_t* key, int32_t* seg_rows,
                                        int32_t* blocks_per_cu, int32_t* max_blocks_per_cu);

@@ -214,7 +214,6 @@ struct itc_plan {
   // convolution tile shape per class key (set by the autotuning hook; 0 =
   // default): target segment rows and workgroups per compute unit
   std::vector<int> key_seg, key_per;
-  int conv_launches = 0;  // classes with a launch of their own
   size_t tile_cap = 0;  // capacity of d_tiles (the most tiles any shape gives)
   // fit schedule: workgroup g of the fit launch (fit_grid workgroups) takes
   // the images fit_list[fit_begin[g] .. fit_begin[g + 1]) in turn
@@ -361,7 +360,6 @@ static void build_conv_tiles(itc_plan* p) {
   p->launch_end.clear();
   p->launch_grid.clear();
   p->launch_split.clear();
-  p->conv_launches = 0;
   for (int key = 0; key < PLAN_NKEYS; ++key)
     if (!by_class[key].empty()) p->cls.push_back(key);
   const int cus = device_cus();
@@ -374,7 +372,6 @@ static void build_conv_tiles(itc_plan* p) {
   };
   // The tiles of the classes `keys`, in that order: one launch, or one a group with the group's weights read before.
   auto add_launch = [&](int launch_key, const std::vector<int>& keys, int per) {
-    ++p->conv_launches;
     std::vector<char> used(p->n, 0);
     for (int key : keys)
       for (const ConvTile& t : by_class[key]) used[t.img] = 1;
@@ -749,7 +746,7 @@ int32_t itc_lattice_plan_size(const itc_plan* p) { return p ? p->n : -1; }
 
 int32_t itc_lattice_plan_conv_classes(const itc_plan* p) { return p ? (int32_t)p->cls.size() : -1; }
 
-int32_t itc_lattice_plan_conv_launches(const itc_plan* p) { return p ? p->conv_launches : -1; }
+int32_t itc_lattice_plan_conv_launches(const itc_plan* p) { return p ? (int32_t)p->launch_key.size() : -1; }
 
 itc_status itc_lattice_plan_conv_class(const itc_plan* p, int32_t c, int32_t* key, int32_t* seg_rows,
                                        int32_t* blocks_per_cu, int32_t* max_blocks_per_cu) {

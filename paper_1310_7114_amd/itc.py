@@ -611,7 +611,8 @@ class BatchPlan:
         return out
 
     def conv_launches(self) -> int:
-        """Kernel launches of one `precompute` (one for all 8-bit images of aligned rows)."""
+        """Kernel launches of one `precompute` (one for all 8-bit images of aligned rows, or two a group of
+        weights that are read ahead)."""
         return int(load().itc_lattice_plan_conv_launches(self.handle))
 
     def set_conv_shape(self, key: int, seg_rows: int = 0, blocks_per_cu: int = 0):

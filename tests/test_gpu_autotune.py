@@ -1,6 +1,8 @@
 """Autotuning of the batched convolution's tile shapes (GPU): the maps are
 bitwise the same for every segment height and workgroup count, and the tuned
 plan gives the default plan's results."""
+import ctypes
+
 import pytest
 import torch
 
@@ -111,6 +113,25 @@ def test_graph_captured_after_tuning_replays_exactly(gpu_lib, tmp_path):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(w, ref[0]) and torch.equal(sx, ref[1]) and torch.equal(d, ref[2])
+
+
+def test_conv_launches_counts_every_kernel(gpu_lib):
+    """The launch count of a plan is the number of kernels one `precompute` runs (read off a capture): one for a
+    small plan, two a group where 320 MiB of weights are read ahead."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    for plan in (gpu_lib.BatchPlan.for_stack(3, 200, 300, 1, 1.0, dtype=torch.uint8),
+                 gpu_lib.BatchPlan.for_stack(3, 200, 301, 1, 1.0, dtype=torch.uint8),
+                 gpu_lib.BatchPlan.for_stack(5, 8192, 8192, 1, 0.6, dtype=torch.uint8)):
+        n = sum(h * w for h, w in plan.shapes)
+        x = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        plan.precompute(weights=x)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g):
+            plan.precompute(weights=x)
+        nodes = ctypes.c_size_t()
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+        assert plan.conv_launches() == nodes.value
 
 
 def test_bad_shapes_are_rejected(gpu_lib):
