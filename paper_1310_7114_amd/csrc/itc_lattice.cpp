@@ -211,6 +211,8 @@ struct itc_plan {
   std::vector<int> launch_key, launch_begin, launch_end, launch_grid;
   std::vector<itc::XcdSplit> launch_split;  // XCD sublists of each launch (offsets from its first tile)
   int mx_max_ra = 0;  // largest aligned radius of the matrix-core images
+  std::vector<int> conv_group;               // group of every image of the 8-bit launch, each a launch of its own
+  std::vector<std::vector<ConvTile>> ahead;  // per group: list entries that read its weights ahead, or none
   // convolution tile shape per class key (set by the autotuning hook; 0 =
   // default): target segment rows and workgroups per compute unit
   std::vector<int> key_seg, key_per;
@@ -296,42 +298,106 @@ static int class_occupancy(const itc_plan* p, int key) {
 // Reading ahead. HBM loses time to every change between reads and writes: beside
 // the map stores the weights of the 8-bit convolution, which the stores bound,
 // cost three times what they do alone, unless the memory-side cache (256 MB) has
-// them. Weights that do not fit it are read in groups of half its size, in a
+// them. Weights that do not fit it are read in groups of at most half its size, in a
 // launch of reads only before the group's tiles, which then find them there.
 // 1,400 silhouettes (360 MB): 1.15 -> 1.09 ms; 400 x 1024^2 bytes 1.30 -> 1.25; at
 // 256 MB 0.79 either way; groups of 64 MB 1.11, of 192 MB 1.15. The FP32 classes
 // lose by it (64 x 1024^2 weights, 256 MB: 0.29 -> 0.31 ms): they share their
-// bound with the matrix unit.
+// bound with the matrix unit. Images above a group's size come last, not read
+// ahead.
 constexpr int64_t READ_AHEAD_MIN = 256ll << 20, READ_AHEAD_GROUP = 128ll << 20;
 
+using ByteRange = std::pair<int64_t, int64_t>;
+
+// Bytes of an image's weights without the gaps of its rows, and the range that holds them.
 static int64_t weight_bytes(const ImageDesc& im) {
+  return (int64_t)im.H * im.W * (im.wdtype == 0 ? 1 : (im.wdtype == 1 ? 4 : 8));
+}
+static ByteRange weight_range(const ImageDesc& im) {
   const int64_t esz = im.wdtype == 0 ? 1 : (im.wdtype == 1 ? 4 : 8);
-  return ((int64_t)(im.H - 1) * im.pitch + im.W) * esz;
+  return {im.weight_off, im.weight_off + ((int64_t)(im.H - 1) * im.pitch + im.W) * esz};
 }
 
-static int plan_read_groups(int64_t bytes) {
-  return bytes > READ_AHEAD_MIN ? (int)((bytes + READ_AHEAD_GROUP - 1) / READ_AHEAD_GROUP) : 1;
-}
-
-// About `pieces` list entries of equal size (img 16-byte units from byte 16 s0 of the weights) that cover the ranges.
-// Gaps below a page are read as well: each of their bytes shares a page with a weight.
-static std::vector<ConvTile> read_pieces(std::vector<std::pair<int64_t, int64_t>>& ranges, int pieces) {
+// The ranges in order, joined across gaps below a page: each byte of such a gap shares a page with a weight.
+static std::vector<ByteRange> merge_ranges(std::vector<ByteRange> ranges) {
   std::sort(ranges.begin(), ranges.end());
-  std::vector<std::pair<int64_t, int64_t>> merged;
-  int64_t total = 0;
-  for (const auto& r : ranges) {
+  std::vector<ByteRange> merged;
+  for (const ByteRange& r : ranges) {
     if (!merged.empty() && r.first < merged.back().second + 4096)
       merged.back().second = std::max(merged.back().second, r.second);
     else
       merged.push_back(r);
   }
-  for (const auto& r : merged) total += r.second - r.first;
+  return merged;
+}
+static int64_t range_bytes(const std::vector<ByteRange>& ranges) {
+  int64_t total = 0;
+  for (const ByteRange& r : ranges) total += r.second - r.first;
+  return total;
+}
+
+// About `pieces` list entries of equal size (img 16-byte units from byte 16 s0 of the weights) that cover the ranges.
+static std::vector<ConvTile> read_pieces(const std::vector<ByteRange>& merged, int pieces) {
   std::vector<ConvTile> out;
-  const int64_t piece = (total / pieces + 16) / 16 * 16;
-  for (const auto& r : merged)
+  const int64_t piece = (range_bytes(merged) / pieces + 16) / 16 * 16;
+  for (const ByteRange& r : merged)
     for (int64_t a = (r.first + 15) / 16 * 16; a + 16 <= r.second; a += piece)
       if (a / 16 <= INT32_MAX) out.push_back(ConvTile{(int32_t)(std::min(piece, r.second - a) / 16), 0, (int32_t)(a / 16), 0});
   return out;
+}
+
+// Groups of the 8-bit launch: conv_group of every image and, per group, the list entries that read it ahead
+// (none: not read). One group, not read, unless the images of at most a group's size hold more weights than
+// READ_AHEAD_MIN (bytes that several images share count once) and every group is nearly all weights: views of a
+// wide buffer would be read with the gaps of their rows.
+static void plan_read_ahead(itc_plan* p) {
+  p->conv_group.assign(p->n, 0);
+  p->ahead.assign(1, {});
+  std::vector<ByteRange> all;
+  int64_t total = 0;
+  bool large = false;
+  auto taken = [&](int i) { return class_key_of(p->images[i]) >= itc::CONV_MX_CLASS; };
+  for (int i = 0; i < p->n; ++i) {
+    if (!taken(i)) continue;
+    if (weight_bytes(p->images[i]) > READ_AHEAD_GROUP) {
+      large = true;
+      continue;
+    }
+    all.push_back(weight_range(p->images[i]));
+    total += weight_bytes(p->images[i]);
+  }
+  if (total <= READ_AHEAD_MIN || range_bytes(merge_ranges(all)) <= READ_AHEAD_MIN) return;
+  // equal shares in the images' order; a group is closed before it would exceed its size
+  const int64_t share = total / ((total + READ_AHEAD_GROUP - 1) / READ_AHEAD_GROUP);
+  std::vector<int> group(p->n, 0);
+  std::vector<std::vector<ByteRange>> ranges(1);
+  std::vector<int64_t> held(1, 0);
+  int64_t before = 0;
+  for (int i = 0; i < p->n; ++i) {
+    const int64_t b = weight_bytes(p->images[i]);
+    if (!taken(i) || b > READ_AHEAD_GROUP) continue;
+    if (held.back() > 0 && (held.back() + b > READ_AHEAD_GROUP || before >= share * (int64_t)held.size())) {
+      held.push_back(0);
+      ranges.push_back({});
+    }
+    group[i] = (int)held.size() - 1;
+    held.back() += b;
+    ranges.back().push_back(weight_range(p->images[i]));
+    before += b;
+  }
+  std::vector<std::vector<ConvTile>> ahead;
+  for (size_t g = 0; g < ranges.size(); ++g) {
+    const std::vector<ByteRange> merged = merge_ranges(std::move(ranges[g]));
+    if (range_bytes(merged) > held[g] + held[g] / 4) return;  // row padding, not other columns
+    ahead.push_back(read_pieces(merged, 4 * device_cus()));
+  }
+  if (large) {
+    for (int i = 0; i < p->n; ++i)
+      if (taken(i) && weight_bytes(p->images[i]) > READ_AHEAD_GROUP) group[i] = (int)ahead.size();
+    ahead.push_back({});
+  }
+  p->conv_group = std::move(group);
+  p->ahead = std::move(ahead);
 }
 
 static void build_conv_tiles(itc_plan* p) {
@@ -372,29 +438,12 @@ static void build_conv_tiles(itc_plan* p) {
   };
   // The tiles of the classes `keys`, in that order: one launch, or one a group with the group's weights read before.
   auto add_launch = [&](int launch_key, const std::vector<int>& keys, int per) {
-    std::vector<char> used(p->n, 0);
-    for (int key : keys)
-      for (const ConvTile& t : by_class[key]) used[t.img] = 1;
-    int64_t total = 0;
-    for (int i = 0; i < p->n; ++i)
-      if (used[i]) total += weight_bytes(p->images[i]);
-    const int ngroups = launch_key >= itc::CONV_MX_CLASS ? plan_read_groups(total) : 1;
-    std::vector<int> group(p->n, 0);
-    int64_t before = 0;
-    for (int i = 0; i < p->n; ++i) {
-      group[i] = (int)std::min<int64_t>(ngroups - 1, before * ngroups / std::max<int64_t>(1, total));
-      if (used[i]) before += weight_bytes(p->images[i]);
-    }
-    for (int g = 0; g < ngroups; ++g) {
+    const bool groups = launch_key >= itc::CONV_MX_CLASS;
+    for (int g = 0; g < (groups ? (int)p->ahead.size() : 1); ++g) {
       int begin = (int)p->tiles.size();
-      if (ngroups > 1) {
-        std::vector<std::pair<int64_t, int64_t>> ranges;  // byte ranges of the group's weights
-        for (int i = 0; i < p->n; ++i)
-          if (used[i] && group[i] == g)
-            ranges.push_back({p->images[i].weight_off, p->images[i].weight_off + weight_bytes(p->images[i])});
-        const std::vector<ConvTile> ahead = read_pieces(ranges, 4 * cus);
-        p->tiles.insert(p->tiles.end(), ahead.begin(), ahead.end());
-        if (!ahead.empty()) launch(CONV_READ, begin, (int)ahead.size(), itc::XcdSplit{});
+      if (groups && !p->ahead[g].empty()) {
+        p->tiles.insert(p->tiles.end(), p->ahead[g].begin(), p->ahead[g].end());
+        launch(CONV_READ, begin, (int)p->ahead[g].size(), itc::XcdSplit{});
         begin = (int)p->tiles.size();
       }
       std::vector<std::vector<ConvTile>> sub(itc::CONV_XCDS);
@@ -404,7 +453,7 @@ static void build_conv_tiles(itc_plan* p) {
         const std::vector<int64_t>& cost = cost_of[key];
         std::vector<int> idx;
         for (int k = 0; k < (int)tiles.size(); ++k)
-          if (group[tiles[k].img] == g) idx.push_back(k);
+          if (!groups || p->conv_group[tiles[k].img] == g) idx.push_back(k);
         std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return cost[x] > cost[y]; });
         // deal the segment rows (runs of tiles of one image and segment, adjacent after the sort) to the XCD
         // sublists, least loaded first
@@ -692,13 +741,8 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
   p->key_per.assign(PLAN_NKEYS, 0);
   for (const ImageDesc& im : p->images)
     if (class_key_of(im) >= itc::CONV_MX_CLASS) p->mx_max_ra = std::max(p->mx_max_ra, itc::conv_mx_radius(im.rclass));
-  {
-    int64_t bytes = 0;
-    for (const ImageDesc& im : p->images) bytes += weight_bytes(im);
-    // pieces read ahead: four a compute unit and group, and two a gap between images
-    if (plan_read_groups(bytes) > 1)
-      p->tile_cap += (size_t)(bytes / READ_AHEAD_GROUP + 1) * 4 * (size_t)device_cus() + 2 * (size_t)p->n;
-  }
+  plan_read_ahead(p);
+  for (const auto& a : p->ahead) p->tile_cap += a.size();
   build_conv_tiles(p);
   const int cus = device_cus();
   int fper = itc::fit_blocks_per_cu(false, p->m_max, p->max_passes);

@@ -134,6 +134,66 @@ def test_conv_launches_counts_every_kernel(gpu_lib):
         assert plan.conv_launches() == nodes.value
 
 
+MIB = 1 << 20
+
+
+def stack_plan(itc, shapes, woffs=None, pitches=None):
+    """A plan over uint8 images at the given byte offsets and pitches (a packed stack by default)."""
+    n = len(shapes)
+    return itc.BatchPlan(None, [1] * n, [0.6] * n, [0] * n, _shapes=shapes, _dtype=torch.uint8, _woffs=woffs,
+                         _pitches=pitches)
+
+
+def views(side, rows, cols, by_columns):
+    """(shapes, offsets, pitches) of the rows x cols views that tile a side x side buffer."""
+    at = [(u, v) for u in range(0, side, rows) for v in range(0, side, cols)]
+    if by_columns:
+        at.sort(key=lambda a: a[::-1])
+    return [(rows, cols)] * len(at), [u * side + v for u, v in at], [side] * len(at)
+
+
+READ_AHEAD = [
+    # 256 MiB of weights in views whose rows are 16,384 bytes apart (with the gaps of every row they span 34 GB)
+    ("views_256MiB", lambda: views(16384, 128, 128, False), 1),
+    # 400 MiB: the views row by row fill whole bands of the buffer; column by column a group would read all of it
+    ("views_by_rows", lambda: views(20480, 1024, 1024, False), 8),
+    ("views_by_columns", lambda: views(20480, 1024, 1024, True), 1),
+    # one image 300 times is one image's bytes
+    ("one_image_300_times", lambda: ([(1024, 1024)] * 300, [0] * 300, [1024] * 300), 1),
+    # above a group's size: not read ahead; small images beside one: three groups of at most 128 MiB, then the large one
+    ("large_images", lambda: ([(12800, 12800)] * 2, None, None), 1),
+    ("mixed", lambda: ([(6400, 6400)] * 4 + [(12800, 12800)] + [(6400, 6400)] * 4, None, None), 7),
+    ("row_padding", lambda: ([(1000, 1000)] * 400, None, [1024] * 400), 6),  # 381 MiB without the padding
+]
+
+
+@pytest.mark.parametrize("name,build,launches", READ_AHEAD, ids=[c[0] for c in READ_AHEAD])
+def test_read_ahead_groups(gpu_lib, name, build, launches):
+    """Weights above 256 MiB are read ahead in groups of at most 128 MiB where a group's bytes are weights, not the
+    gaps between the rows of views; the maps are those of the images alone, also after a change of the tile shape."""
+    shapes, woffs, pitches = build()
+    plan = stack_plan(gpu_lib, shapes, woffs, pitches)
+    assert plan.conv_launches() == launches
+    end = max(int(o) + (h - 1) * p + w for (h, w), o, p in zip(shapes, plan.weight_off, plan.pitches))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randint(0, 256, (end,), generator=g, device="cuda", dtype=torch.uint8)
+    some = sorted({0, len(shapes) // 3, len(shapes) - 1})
+
+    for key in [None] + [c["key"] for c in plan.conv_classes()]:
+        if key is not None:
+            plan.set_conv_shape(key, 512, 1)
+            assert plan.conv_launches() == launches
+        plan.maps.zero_()
+        plan.precompute(weights=x)
+        for i in some:
+            (h, w), p, o = shapes[i], plan.pitches[i], int(plan.weight_off[i])
+            img = x[o: o + (h - 1) * p + w].as_strided((h, w), (p, 1))
+            one = gpu_lib.precompute(img, 0.6)
+            got = plan.maps_of(i)
+            for a, b in zip(got.planes(), one.planes()):
+                assert torch.equal(a, b)
+
+
 def test_bad_shapes_are_rejected(gpu_lib):
     plan, _ = make_plan(gpu_lib, S.config3_cases(indices=range(4)))
     key = plan.conv_classes()[0]["key"]
