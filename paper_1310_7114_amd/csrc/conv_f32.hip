@@ -29,11 +29,13 @@
 //
 // A zero tap times a non-finite value is not zero. Every output of a 16 x 16 tile
 // sees every value of its window, so such a value (a weight that is not finite, an
-// overflow) leaves none of the tile's A or M_v finite; a wave that finds one
-// computes its columns of the segment again from the window sums, so that the
-// value reaches exactly the pixels within R of it. The test rides on the S_X
+// overflow) leaves none of the tile's A or M_v finite; a wave that finds one makes its
+// columns of the S_X row groups concerned again from the window sums (rows_by_windows),
+// so that the value reaches exactly the pixels within R of it. The test rides on the S_X
 // sum: as eight multiply-adds per row pass and a vote of the workgroup it took
-// 60 us of 280 (R = 4, below).
+// 60 us of 280 (R = 4, below). One such weight, with and without: 64 images of 1024^2
+// 0.29 and 0.28 ms at R = 12, 0.67 and 0.48 at R = 32; one image 0.06 and 0.013, 0.23
+// and 0.026 (a sum over the whole window for each pixel of the segment: 10.3 at R = 32).
 //
 // Bound by memory (4 B read and 12 B written per pixel) up to R of about 8, then
 // by the matrix unit. 64 x 1024^2 FP32 weights: R = 4 209 us (5.1 TB/s; 290 us
@@ -75,7 +77,6 @@ struct CfGeom {
   static constexpr int WGS = RA <= 24 ? 3 : 2;               // workgroups per compute unit: LDS allows no more
   static constexpr size_t SMEM = (2 * (size_t)STAGE + 2 * (size_t)RING) * sizeof(float);
   static_assert(RINGP / 4 % 2 == 1 && SWP / 4 % 2 == 1, "bank-spread pitches");
-  static_assert(16 * RINGP >= 128, "a wave's ring holds the taps");
   static_assert(REM == 0 || REM == 8, "K is a multiple of eight");
 };
 
@@ -90,57 +91,119 @@ __device__ __forceinline__ constexpr int k_of(int st, int q) {
   return st < 4 * G::NG ? 16 * (st / 4) + 4 * q + st % 4 : 16 * G::NG + 2 * q + (st - 4 * G::NG);
 }
 
-// A wave's 16 columns of the segment from the window sums themselves, for
-// segments with non-finite values: every pixel sums its rows with g and tg,
-// then over the rows; t = 0 has no tg term. `taps` is LDS of this wave.
-template <typename WT>
-__device__ __forceinline__ void segment_by_windows(const ImageDesc& im, int strip, int s0, int seg_end,
-                                                   const char* wbase, char* mbase, float* taps) {
+// A wave's 16 columns of the S_X row groups of [s0, seg_end) that see a value that is not finite (this wave's partials,
+// written before, are not finite) from the window sums themselves: vector FMAs over the taps of the true radius only,
+// through this wave's columns of the ring like the products of cf_segment. t = 0 has no tg term. Lane (n, q) makes
+// rows 4q .. 4q + 3 of column n.
+template <int RA, typename WT>
+__device__ __forceinline__ void rows_by_windows(const ImageDesc& im, int strip, int s0, int seg_end, const char* wbase,
+                                                char* mbase, float* ring) {
+  using G = CfGeom<RA>;
   const int H = im.H, W = im.W, R = im.R;
-  const WT* x = reinterpret_cast<const WT*>(wbase + im.weight_off);
+  constexpr uint32_t esz = sizeof(WT);
+  const uint32_t rowbytes = (uint32_t)im.pitch * esz;
+  const rsrc_t wres = make_rsrc(wbase + im.weight_off, (uint32_t)H * rowbytes);
   float* maps = reinterpret_cast<float*>(mbase + im.map_off);
   const float scale = (float)im.scale;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
-  const int lane = tid & 63, wave = tid >> 6;
-  if (lane <= R) {
-    const double gl = exp(-0.5 / (im.sigma * im.sigma) * (double)(lane * lane));
-    taps[lane] = (float)gl;
-    taps[64 + lane] = (float)((double)lane * gl);
-  }
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  const int v = strip * CONV_TW + 16 * wave + (lane & 15);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  const int v = strip * CONV_TW + 16 * wave + n;
+  const double gl = exp(-0.5 / (im.sigma * im.sigma) * (double)(lane * lane));
+  const float gT = (float)gl, tgT = (float)((double)lane * gl);  // the taps |t| = lane
   double* part = reinterpret_cast<double*>(mbase + im.map_off + im.part_off) + (int64_t)strip * im.nsxg * SX_SLOTS + wave;
-  double sxd = 0.0;
-#pragma unroll 1
-  for (int o0 = s0; o0 < seg_end; o0 += 4) {
-    const int o = o0 + (lane >> 4);
-    if (o < seg_end && v < im.npanels * MAP_PANEL) {
-      float a = 0.f, mu = 0.f, mv = 0.f;
-#pragma unroll 1
-      for (int y = max(o - R, 0); y <= min(o + R, H - 1); ++y) {
-        const WT* xr = x + (int64_t)y * im.pitch;
-        float r0 = 0.f, r1 = 0.f;
-#pragma unroll 1
-        for (int c = max(v - R, 0); c <= min(v + R, W - 1); ++c) {
-          const int t = v - c, at = t < 0 ? -t : t;
-          const float h = (float)xr[c] * scale, tg = taps[64 + at];
-          r0 = fmaf(taps[at], h, r0);
-          if (t) r1 = fmaf(t < 0 ? -tg : tg, h, r1);
-        }
-        const int t = o - y, at = t < 0 ? -t : t;
-        const float g = taps[at], tg = taps[64 + at];
-        a = fmaf(g, r0, a);
-        mv = fmaf(g, r1, mv);
-        if (t) mu = fmaf(t < 0 ? -tg : tg, r0, mu);
-      }
-      const int64_t i = map_index(H, o, v);
-      maps[i] = a;
-      maps[im.plane + i] = mu;
-      maps[2 * im.plane + i] = mv;
-      if (v < W) sxd += (double)((float)x[(int64_t)o * im.pitch + v] * a);
+  float* col = ring + (16 * wave + n) * G::RINGP;
+  // the rows from the first such group to the last
+  int r0 = seg_end, r1 = s0;
+  for (int o = s0; o < seg_end; o += SX_ROWS) {
+    const double tot = lane == 0 ? part[(int64_t)(o / SX_ROWS) * SX_SLOTS] : 0.0;  // as this lane wrote it
+    if (__any(!(fabs(tot) < INFINITY))) {
+      r0 = min(r0, o);
+      r1 = min(o + SX_ROWS, seg_end);
     }
-    if ((o0 + 4) % SX_ROWS == 0 || o0 + 4 >= seg_end) {  // uniform
+  }
+  const int nout = (r1 - r0 + CF_CH - 1) / CF_CH;
+  double sxd = 0.0;
+  wave_lds_order();
+#pragma unroll 1
+  for (int j = 0; j < G::J0 + nout; ++j) {
+    uint32_t off[4];
+    f4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int y = r0 - RA + CF_CH * j + 4 * q + i;
+      off[i] = y >= 0 && y < H ? (uint32_t)y * rowbytes : BUF_OOB;
+    }
+    constexpr int NT = 4;  // taps whose loads are in flight together; past R they read 0
+#pragma unroll 1
+    for (int t0 = -R; t0 <= R; t0 += NT) {  // uniform
+      float h[NT][4];
+#pragma unroll
+      for (int e = 0; e < NT; ++e) {
+        const int c = v - t0 - e;
+        const bool in = t0 + e <= R && c >= 0 && c < W;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[e][i] = (float)buf_load<WT>(wres, in ? off[i] + (uint32_t)c * esz : BUF_OOB, 0) * scale;
+      }
+#pragma unroll
+      for (int e = 0; e < NT; ++e) {
+        const int t = t0 + e, at = t < 0 ? -t : t;
+        const float g = lane_value(gT, at), tg = t < 0 ? -lane_value(tgT, at) : lane_value(tgT, at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s0[i] = fmaf(g, h[e][i], s0[i]);
+          if (t) s1[i] = fmaf(tg, h[e][i], s1[i]);
+        }
+      }
+    }
+    float* rp = col + (j % G::NB) * CF_CH + 4 * q;
+    *reinterpret_cast<f4_t*>(rp) = s0;
+    *reinterpret_cast<f4_t*>(rp + G::RING) = s1;
+    wave_lds_order();
+    const int jo = j - G::J0;
+    if (jo < 0) continue;
+    float a[4] = {}, mu[4] = {}, mv[4] = {};
+    int slot = (jo % G::NB) * CF_CH + 4 * q + RA - R;  // ring row of row 4q's t = R
+    float y0[4] = {}, y1[4] = {};  // the rows of the four outputs at one t
+    auto next = [&]() {
+      const float* y = col + (slot < G::NB * CF_CH ? slot : slot - G::NB * CF_CH);
+      ++slot;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        y0[i] = y0[i + 1];
+        y1[i] = y1[i + 1];
+      }
+      y0[3] = y[0];
+      y1[3] = y[G::RING];
+    };
+    next();
+    next();
+    next();
+#pragma unroll 1
+    for (int t = R; t >= -R; --t) {  // uniform
+      next();
+      const int at = t < 0 ? -t : t;
+      const float g = lane_value(gT, at), tg = t < 0 ? -lane_value(tgT, at) : lane_value(tgT, at);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[i] = fmaf(g, y0[i], a[i]);
+        mv[i] = fmaf(g, y1[i], mv[i]);
+        if (t) mu[i] = fmaf(tg, y0[i], mu[i]);
+      }
+    }
+    const int o0 = r0 + CF_CH * jo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int o = o0 + 4 * q + i;
+      if (o >= r1 || v >= im.npanels * MAP_PANEL) continue;
+      const int64_t m = map_index(H, o, v);
+      maps[m] = a[i];
+      maps[im.plane + m] = mu[i];
+      maps[2 * im.plane + m] = mv[i];
+      if (v < W) sxd += (double)((float)buf_load<WT>(wres, (uint32_t)o * rowbytes + (uint32_t)v * esz, 0) * a[i]);
+    }
+    if ((jo + 1) % (SX_ROWS / CF_CH) == 0 || jo == nout - 1) {  // uniform
       const double tot = wave_sum(sxd);
       if (lane == 0) part[(int64_t)(o0 / SX_ROWS) * SX_SLOTS] = tot * im.scale;
       sxd = 0.0;
@@ -357,8 +420,7 @@ __device__ __forceinline__ void cf_segment(const ImageDesc& im, int strip, int s
     chunk(j + 1, std::integral_constant<int, 1>{});
   }
   if (j < nchunks) chunk(j, std::integral_constant<int, 0>{});
-  if (__builtin_amdgcn_readfirstlane(odd))
-    segment_by_windows<WT>(im, strip, s0, seg_end, wbase, mbase, ring + 16 * wave * G::RINGP);
+  if (__builtin_amdgcn_readfirstlane(odd)) rows_by_windows<RA, WT>(im, strip, s0, seg_end, wbase, mbase, ring);
 }
 
 // One segment for the image's stored weight type (one uniform branch per segment).

@@ -167,6 +167,47 @@ def test_maps_fp32_nonfinite_reach(gpu_lib, R, value):
             assert not np.isfinite(got[0][near]).any()
 
 
+@pytest.mark.parametrize("wdtype", [np.float32, np.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("R", [1, 5, 8, 16, 29, 32])
+def test_maps_fp32_nonfinite_rows(gpu_lib, R, wdtype):
+    """Values that are not finite in several S_X row groups of a segment and between them: every pixel farther than R
+    from all of them has the value of the weights without them, every other none in A; S_X has none."""
+    rng = np.random.default_rng(R)
+    clean = rng.uniform(0, 1, (400, 90)).astype(wdtype)
+    bad = clean.copy()
+    near = np.zeros(clean.shape, bool)
+    for u, v, x in [(3, 5, np.inf), (131, 63, np.nan), (139, 88, -np.inf), (255, 15, np.inf), (256, 16, np.nan)]:
+        bad[u, v] = x
+        clean[u, v] = 0.0
+        near[max(u - R, 0): u + R + 1, max(v - R, 0): v + R + 1] = True
+    _, got, sx = gpu_maps(gpu_lib, bad, R / 3.0, 0.5, R)
+    for x, r in zip(got, ref_maps(clean.astype(np.float64) * 0.5, R / 3.0, R)):
+        assert np.abs(np.where(near, 0.0, x - r)).max() <= 1e-5 * np.abs(r).max()
+    assert not np.isfinite(got[0][near]).any() and not np.isfinite(sx)
+
+
+def test_maps_fp32_nonfinite_time(gpu_lib):
+    """One weight that is not finite costs its row groups a second pass over their windows' rows and columns, not a
+    sum over the whole window for every pixel (20 ms here)."""
+    x = torch.rand((1024, 1024), device=DEV)
+    m = gpu_lib.precompute(x, 32 / 3.0)
+
+    def ms():
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = 1e9
+        for _ in range(5):
+            a.record()
+            gpu_lib.precompute(x, 32 / 3.0, out=m)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    finite = ms()
+    x[300, 77] = float("nan")
+    assert ms() <= 10 * finite + 1.0
+
+
 def test_maps_full_size_512(gpu_lib):
     case = S.config2_case()
     _, got, sx = gpu_maps(gpu_lib, case.img, case.sigma)
