@@ -191,15 +191,8 @@ __global__ void __launch_bounds__(GNT) grad_weights_tiles_kernel(const ImageDesc
   __shared__ GradSmem<T> sm;
   int cur = -1;  // image whose S_XW is held
   double S_XW = 0.0;
-  const int first = blockIdx.x * per, n = min(ntiles - first, per);
-  if (n <= 0) return;
-  // Runs of whole tile rows would all stand at the same column at a time, and where the rows are a multiple of
-  // 4 KiB apart the chip's stores then meet in a few memory channels: such runs start in turn at every column
-  // (64 x 1024^2, M = 256: 148 us, 124 in turn; other sizes lose 2 to 3 % by it, the run's images being split).
-  const int W0 = images[tiles[first].img].W;
-  const int turn = W0 % 1024 == 0 && per % (W0 / GT) == 0 ? (int)blockIdx.x % n : 0;
-  for (int q = 0; q < n; ++q) {
-    const GradTile t = tiles[first + (q + turn < n ? q + turn : q + turn - n)];
+  for (int i = blockIdx.x * per; i < min(ntiles, ((int)blockIdx.x + 1) * per); ++i) {
+    const GradTile t = tiles[i];
     const ImageDesc im = images[t.img];
     if (t.img != cur) {  // uniform
       S_XW = image_sxw<T>(im, ga, sm);

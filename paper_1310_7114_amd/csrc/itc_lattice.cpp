@@ -727,8 +727,15 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
     p->max_passes = std::max(p->max_passes, itc::fit_passes_of(im.M));
     p->tile_cap += (size_t)im.nstrips * (size_t)((im.H + PLAN_SEG_MIN - 1) / PLAN_SEG_MIN);
     fit_cost[i] = (double)(im.iters + 1) * im.M * (im.M + 16.0);
-    for (int u0 = 0; u0 < im.H; u0 += 64)
-      for (int v0 = 0; v0 < im.W; v0 += 64) p->gtiles.push_back(itc::GradTile{i, u0, v0, 0});
+    // Gradient tiles, row by row. Where rows are a multiple of 4 KiB apart, a tile column is one place among the
+    // memory channels whatever its row, and workgroups whose runs start alike (whole tile rows, or halves) would store
+    // to few of them at a time: every tile row starts at another column of each 4 KiB. us in order and so, M = 64:
+    // 64 images of 1024^2 135 and 114, 32 52.8 and 50.8, 128 239 and 224; 64 of 1024 x 2048 253 and 230, 32 of
+    // 1024 x 4096 255 and 254. Other widths shift with the row by themselves (64 of 1023 wide: 170 and 188).
+    const int ncols = (im.W + 63) / 64, turn = im.W * sizeof(float) % 4096 == 0 ? 1 : 0;
+    for (int r = 0; 64 * r < im.H; ++r)
+      for (int c = 0; c < ncols; ++c)
+        p->gtiles.push_back(itc::GradTile{i, 64 * r, 64 * ((c & ~15) | ((c + turn * r) & 15)), 0});
     p->all_u8 = p->all_u8 && im.wdtype == ITC_U8;
     p->w_max = std::max(p->w_max, im.W);
     p->h_max = std::max(p->h_max, im.H);

@@ -97,6 +97,28 @@ def test_batched_backward_equals_single(gpu_lib):
         assert float(sx[i]) == float(m.s_x[0])
 
 
+def test_batched_tile_order(gpu_lib):
+    """Widths whose rows are a multiple of 4 KiB apart (tile rows start at another column each), others, and ragged
+    heights in one plan: every pixel's gradient is written and is the image's alone."""
+    rng = np.random.default_rng(8)
+    shapes = [(70, 1024), (200, 2048), (129, 1000), (64, 64), (1030, 1024), (65, 3072)]
+    ws = [rng.uniform(0, 1, (20, 2)) * np.array(s) for s in shapes]
+    imgs = [torch.from_numpy(rng.uniform(0.1, 1, s).astype(np.float32)) for s in shapes]
+    plan = gpu_lib.BatchPlan(imgs, [20] * 6, [3.0] * 6, [0] * 6)
+    w = plan.pack_codebooks([torch.from_numpy(x) for x in ws])
+    plan.precompute()
+    sx = torch.empty(6, dtype=torch.float64, device="cuda")
+    plan.fit(w, torch.empty_like(w), s_x=sx)
+    gd = torch.arange(1, 7, dtype=torch.float64, device="cuda")
+    gi = torch.full((plan.weights.numel(),), float("nan"), device="cuda")
+    plan.backward(w, sx, gd, grad_weights=gi)
+    for i, (H, W) in enumerate(shapes):
+        one = gpu_lib.precompute(imgs[i].cuda(), 3.0)
+        _, ref = gpu_lib.divergence_backward(one, plan.unpack(w, i), gd[i: i + 1], want_w=False)
+        off = int(plan.weight_off[i]) // 4
+        assert torch.equal(gi[off: off + H * W].view(H, W), ref), i
+
+
 def test_autograd_function(gpu_lib):
     from paper_1310_7114_amd.autograd import divergence
     cases = [small_case(20 + i, H=96, W=80, M=16, sigma=2.0) for i in range(2)]
