@@ -338,13 +338,13 @@ struct TraceRing {
 // Codebooks of at most FIT_SMALL codevectors, one wave: lanes k P .. k P + P - 1
 // hold codevector k (the same values in each) and take the pair terms of j = p,
 // p + P, .. (p their place among the P), M <= 64 / P. Wh: 64 entries in LDS, padded
-// with FIT_FAR.
+// with FIT_FAR. lane: the caller's opaque one.
 constexpr int FIT_SMALL = 32;
 
 template <typename T, int P, bool TRACE>
-__device__ void fit_small(const ImageDesc& im, const FitImageArgs& a, V2<T>* __restrict__ Wh) {
+__device__ void fit_small(const ImageDesc& im, const FitImageArgs& a, V2<T>* __restrict__ Wh, int lane) {
   constexpr int NJ = 64 / P / P > 1 ? 64 / P / P : 1;  // pair terms of a lane
-  const int M = im.M, lane = threadIdx.x & 63, k = lane / P, p = lane % P;
+  const int M = im.M, k = lane / P, p = lane % P;
   const bool own = k < M, lead = own && p == 0;
   const double s = sqrt(1.4426950408889634 / (2.0 * im.sigma * im.sigma));
   const double cu = 0.5 * im.H, cv = 0.5 * im.W;
@@ -471,13 +471,13 @@ __device__ void fit_image(const ImageDesc& im, const FitImageArgs& a, char* smem
   if (M <= FIT_SMALL) {  // uniform
     if (wave == 0) {
       if (M > 16)
-        fit_small<T, 2, TRACE>(im, a, Wh);
+        fit_small<T, 2, TRACE>(im, a, Wh, lane);
       else if (M > 8)
-        fit_small<T, 4, TRACE>(im, a, Wh);
+        fit_small<T, 4, TRACE>(im, a, Wh, lane);
       else if (M > 4)
-        fit_small<T, 8, TRACE>(im, a, Wh);
+        fit_small<T, 8, TRACE>(im, a, Wh, lane);
       else
-        fit_small<T, 16, TRACE>(im, a, Wh);
+        fit_small<T, 16, TRACE>(im, a, Wh, lane);
     }
     __syncthreads();  // shared memory is reused by the next image
     return;
@@ -682,10 +682,13 @@ __global__ void __launch_bounds__(FIT_NT) fit_image_kernel(ImageDesc im, FitArgs
   fit_image<T, MAXPASS, true>(im, a, smem);
 }
 
-// Waves per SIMD the batched FP32 single-pass fit is compiled for: five
-// (96 registers; a few per-image values go to scratch outside the sweep
-// loop) rather than the four its 110 registers allow, so five workgroups
-// share a compute unit: 3-4 % faster on the 1,400 silhouettes, six 2 %.
+// Waves per SIMD the batched FP32 single-pass fit is compiled for: five (96
+// registers, 19 of them spilled) of the four its registers would allow. ms at
+// four, five and six waves: 1,400 silhouettes 0.68, 0.70, 0.68; 4,000 images with
+// 4 to 255 codevectors 1.66, 1.53, 1.51; 3,000 with 40 0.34, 0.30, 0.32; 8 with 256
+// 0.39, 0.40, 0.39. (54 were spilled, some in the sweep loops, while the one-wave
+// form took its lane from threadIdx: 1,400 images with up to 32 codevectors 0.113 ms,
+// now 0.101.)
 template <typename T, int MAXPASS>
 constexpr int fit_batched_min_waves() {
   return std::is_same<T, float>::value && MAXPASS == 1 ? 5 : 1;
