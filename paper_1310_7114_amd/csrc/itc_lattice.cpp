@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <numeric>
 #include <string>
@@ -677,14 +678,9 @@ itc_status itc_lattice_divergence_backward(const itc_lattice_desc* d, const void
 // ---------------------------------------------------------------------------
 // batched
 // ---------------------------------------------------------------------------
-itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
-  TraceRange trace_range("itc_lattice_plan_create");
-  if (!b || !out) return fail(ITC_E_NULL, "batch and out must be non-NULL");
-  *out = nullptr;
-  if (b->n < 1) return fail(ITC_E_ARG, "batch must hold >= 1 image (got %d)", b->n);
-  if (!b->desc || !b->weight_off || !b->map_off || !b->M || !b->w_off || !b->iters)
-    return fail(ITC_E_NULL, "batch arrays must be non-NULL");
-  itc_plan* p = new (std::nothrow) itc_plan;
+// The body of itc_lattice_plan_create; `p` is the plan while it is built (the lists may throw).
+static itc_status plan_create(const itc_batch* b, itc_plan** out, itc_plan*& p) {
+  p = new (std::nothrow) itc_plan;
   if (!p) return fail(ITC_E_DEVICE, "out of host memory");
   p->n = b->n;
   p->images.resize(b->n);
@@ -793,6 +789,23 @@ itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
   return ok();
 }
 
+itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out) {
+  TraceRange trace_range("itc_lattice_plan_create");
+  if (!b || !out) return fail(ITC_E_NULL, "batch and out must be non-NULL");
+  *out = nullptr;
+  if (b->n < 1) return fail(ITC_E_ARG, "batch must hold >= 1 image (got %d)", b->n);
+  if (!b->desc || !b->weight_off || !b->map_off || !b->M || !b->w_off || !b->iters)
+    return fail(ITC_E_NULL, "batch arrays must be non-NULL");
+  itc_plan* p = nullptr;
+  try {
+    return plan_create(b, out, p);
+  } catch (const std::exception&) {
+    itc_lattice_plan_destroy(p);
+    return fail(ITC_E_DEVICE, "out of host memory for a plan of %d images", b->n);
+  }
+}
+
+
 int32_t itc_lattice_plan_size(const itc_plan* p) { return p ? p->n : -1; }
 
 int32_t itc_lattice_plan_conv_classes(const itc_plan* p) { return p ? (int32_t)p->cls.size() : -1; }
@@ -822,12 +835,19 @@ itc_status itc_lattice_plan_set_conv_shape(itc_plan* p, int32_t key, int32_t seg
   const int top = class_occupancy(p, key), most = key < itc::CONV_MX_CLASS ? std::max(top, 4) : top;
   if (blocks_per_cu < 0 || blocks_per_cu > most)
     return fail(ITC_E_ARG, "workgroups per compute unit %d outside [0, %d]", blocks_per_cu, most);
-  p->key_seg[key] = seg_rows;
-  p->key_per[key] = std::min(blocks_per_cu, top);
-  build_conv_tiles(p);
-  if (p->tiles.size() > p->tile_cap) return fail(ITC_E_DEVICE, "tile list exceeds its capacity");
-  hipError_t e = hipMemcpy(p->d_tiles, p->tiles.data(), sizeof(ConvTile) * p->tiles.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return device_fail(e, "tile upload");
+  try {
+    itc_plan next = *p;  // the plan stays whole if its lists cannot be built
+    next.key_seg[key] = seg_rows;
+    next.key_per[key] = std::min(blocks_per_cu, top);
+    build_conv_tiles(&next);
+    if (next.tiles.size() > next.tile_cap) return fail(ITC_E_DEVICE, "tile list exceeds its capacity");
+    hipError_t e =
+        hipMemcpy(next.d_tiles, next.tiles.data(), sizeof(ConvTile) * next.tiles.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return device_fail(e, "tile upload");
+    *p = std::move(next);
+  } catch (const std::exception&) {
+    return fail(ITC_E_DEVICE, "out of host memory for the plan's tiles");
+  }
   return ok();
 }
 

@@ -3,6 +3,8 @@ and rejects bad arguments on the host before touching the device (CPU only)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -262,3 +264,27 @@ def test_status_strings(itc):
     lib = itc.load()
     assert lib.itc_status_str(0) == b"ok"
     assert lib.itc_status_str(3) == b"unsupported size"
+
+
+@pytest.mark.skipif("ITC_LIB_PATH" in os.environ, reason="a sanitizer's allocator ends the process instead of throwing")
+def test_plan_of_too_many_images_is_an_error():
+    """A plan whose lists do not fit host memory is refused; no C++ exception crosses the C entry (in a child process
+    with little address space)."""
+    code = r"""
+import ctypes, resource, sys
+sys.path.insert(0, ROOT)
+from paper_1310_7114_amd import itc
+lib = itc.load()
+one = itc.make_desc(8, 8, 1.0)
+z = (ctypes.c_int64 * 1)(0)
+m = (ctypes.c_int32 * 1)(1)
+b = itc.Batch(2**31 - 1, ctypes.pointer(one), z, z, m, z, m)
+h = ctypes.c_void_p()
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (1 << 32), used + (1 << 32)))
+print("status", lib.itc_lattice_plan_create(ctypes.byref(b), ctypes.byref(h)), h.value, lib.itc_last_error().decode())
+"""
+    r = subprocess.run([sys.executable, "-c", code.replace("ROOT", repr(ROOT))], cwd=ROOT, capture_output=True, text=True,
+                       timeout=240)
+    assert r.returncode == 0, r.stderr
+    assert "status 4 None out of host memory" in r.stdout, r.stdout
