@@ -136,9 +136,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr())
 
 
+# the raw handle of a device's current stream, where this torch has it: a Stream object per call takes 5 us of a
+# small image's 50
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the raw handle: a Stream object per call takes 5 us of a small image's 50
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 _WDT = {torch.uint8: ITC_U8, torch.float32: ITC_F32, torch.float64: ITC_F64}

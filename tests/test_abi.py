@@ -288,3 +288,16 @@ print("status", lib.itc_lattice_plan_create(ctypes.byref(b), ctypes.byref(h)), h
                        timeout=240)
     assert r.returncode == 0, r.stderr
     assert "status 4 None out of host memory" in r.stdout, r.stdout
+
+
+def test_stream_handle_without_the_raw_getter(itc, monkeypatch):
+    """The current stream's handle where this torch has no raw getter, and with one."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(itc, "_raw_stream", None)
+    monkeypatch.setattr(itc.torch.cuda, "current_stream", lambda: Stream)
+    assert itc._stream().value == 0x1234
+    monkeypatch.setattr(itc, "_raw_stream", lambda device: 0x5678 + device)
+    monkeypatch.setattr(itc.torch.cuda, "current_device", lambda: 3)
+    assert itc._stream().value == 0x567b
