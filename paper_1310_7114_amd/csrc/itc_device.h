@@ -129,18 +129,6 @@ __device__ __forceinline__ double group_sum(double x) {
   return x;
 }
 
-// Min over the 64 lanes of a wave (NaN lanes are ignored unless all are NaN);
-// every lane gets it.
-__device__ __forceinline__ double wave_min(double x) {
-  x = fmin(x, dpp_f64<DPP_QP_1032>(x));
-  x = fmin(x, dpp_f64<DPP_QP_2301>(x));
-  x = fmin(x, dpp_f64<DPP_HALF_MIRROR>(x));
-  x = fmin(x, dpp_f64<DPP_MIRROR>(x));
-  x = fmin(x, dpp_f64<DPP_BCAST15, 0xa>(x));
-  x = fmin(x, dpp_f64<DPP_BCAST31, 0xc>(x));
-  return lane_value(x, 63);
-}
-
 // Max over the 64 lanes of a wave; every lane gets it.
 __device__ __forceinline__ float wave_max(float x) {
   x = fmaxf(x, dpp_f32<DPP_QP_1032>(x));
@@ -207,20 +195,9 @@ __device__ __forceinline__ void buf_store(T v, rsrc_t r, uint32_t voff, uint32_t
                                           r, voff, soff, 0);
 }
 
-// Store of a 32-bit result that nothing of this launch reads: non-temporal, so
-// that it leaves no dirty lines in the caches for what follows to evict.
-template <typename T>
-__device__ __forceinline__ void buf_stream(T v, rsrc_t r, uint32_t voff, uint32_t soff) {
-  static_assert(sizeof(T) == 4, "32-bit results");
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 2);
-}
-
-// Deterministic FP64 sum of n values by one workgroup of nt threads (nt a
-// multiple of 64): thread t adds t, t+nt, ...; then each wave by a fixed xor
-// tree; then the waves in order. `red` is shared scratch of nt/64 doubles.
-// Every thread gets the total.
 // The workgroup total of one FP64 value per thread: each wave by a fixed xor
-// tree, then the waves in order. Every thread gets the total.
+// tree, then the waves in order. `red` is shared scratch of nt/64 doubles (nt
+// threads, a multiple of 64). Every thread gets the total.
 __device__ inline double block_reduce_fixed(double s, double* red) {
   const int nt = blockDim.x, tid = threadIdx.x;
   s = wave_sum(s);
@@ -232,6 +209,8 @@ __device__ inline double block_reduce_fixed(double s, double* red) {
   return t;
 }
 
+// Deterministic FP64 sum of n values by one workgroup of nt threads: thread t
+// adds t, t+nt, ...; then the threads as above.
 template <typename P>
 __device__ inline double block_sum_fixed(const P* p, int64_t n, double* red) {
   const int nt = blockDim.x, tid = threadIdx.x;

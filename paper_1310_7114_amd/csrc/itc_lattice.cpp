@@ -970,7 +970,7 @@ static bool literal_layout(const itc_lattice_desc& d, int32_t M, double omega, i
   L.nvx = (d.height + 15) / 16;
   L.maps = 0;
   L.taps = with_maps ? (maps_bytes_of(d) + 255) / 256 * 256 : 0;
-  L.vx = L.taps + (size_t)(3 * R + 2) * sizeof(double);
+  L.vx = L.taps + (size_t)(R + 1) * sizeof(double);
   L.terms = L.vx + (size_t)L.nvx * sizeof(double);
   L.state = L.terms + (size_t)6 * M * sizeof(double);
   L.total = (L.state + 8 + 255) / 256 * 256;

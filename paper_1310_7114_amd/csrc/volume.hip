@@ -28,7 +28,6 @@
 // LDS (scaled by sqrt(log2 e / 2 sigma^2) and centred on the volume, so each
 // pair is one exp2), FP64 reductions of S_XW and S_W in a fixed order, and the
 // Jacobi update.
-#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <type_traits>
@@ -486,8 +485,8 @@ hipError_t launch_volume_maps_t(const VolumeGeom& vg, const void* x, float* work
   const int64_t n = (int64_t)vg.D * vg.H * vg.W;
   float *Q00 = work, *Q01 = work + n, *Q10 = work + 2 * n;
   const VolTaps tp = make_taps(vg);
-  // the staged tile has 32 + 2R <= 4 SROWS rows of max(64 + 2R, 128) floats: at most 48 KiB
-  const size_t rp = (size_t)std::max(64 + 2 * vg.R, 128) * sizeof(float);
+  // the staged tile has 32 + 2R <= 4 SROWS rows of 128 floats (64 + 2R of them staged): at most 48 KiB
+  constexpr size_t rp = 128 * sizeof(float);
   const dim3 pg((vg.W + 63) / 64, (vg.H + VOL_TR - 1) / VOL_TR, vg.D);
   if (vg.R <= 8)
     hipLaunchKernelGGL((vol_plane_kernel<WT, 12>), pg, dim3(VOL_NT), 48 * rp, s, (const WT*)x, vg, tp, Q00, Q01, Q10);
