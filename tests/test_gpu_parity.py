@@ -147,6 +147,36 @@ def test_maps_fp32_window_edges(gpu_lib, R, wdtype):
         assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
 
 
+@pytest.mark.parametrize("wdtype", [np.float32, np.float64, np.uint8], ids=["f32", "f64", "u8"])
+@pytest.mark.parametrize("R", [1, 2, 3])
+def test_maps_fp32_small_windows(gpu_lib, R, wdtype):
+    """The vector form of the smallest radii, with the bound of the window edges, and its maps in a plan bit for bit."""
+    rng = np.random.default_rng(20 + R)
+    sigma = 0.9 * R
+    t = np.abs(O.taps(sigma, R))
+    imgs = []
+    for H, W in [(1, 1), (2, 3), (15, 17), (16, 64), (17, 65), (40, 128), (33, 61), (257, 130), (321, 19)]:
+        img = rng.integers(0, 256, (H, W)).astype(np.uint8) if wdtype == np.uint8 else rng.uniform(0, 1, (H, W)).astype(wdtype)
+        imgs.append(img)
+        _, got, sx = gpu_maps(gpu_lib, img, sigma, 0.5, R, aligned=False)
+        I = img.astype(np.float64) * 0.5
+        g, tg = t, t * np.abs(np.arange(-R, R + 1))
+        mags = [O.correlate_axis(O.correlate_axis(I, a, 0), b, 1) for a, b in ((g, g), (tg, g), (g, tg))]
+        ref = ref_maps(I, sigma, R)
+        for x, r, m in zip(got, ref, mags):
+            assert np.all(np.abs(x - r) <= (2 * (2 * (R + 3) + 16) + 8) * 2.0 ** -24 * m + 1e-12)
+        assert sx == pytest.approx(float(np.sum(I * ref[0])), rel=1e-6)
+    if wdtype == np.uint8:
+        return  # a plan's 8-bit rows are aligned
+    n = len(imgs)
+    plan = gpu_lib.BatchPlan([torch.from_numpy(i) for i in imgs], [1] * n, [sigma] * n, [0] * n, [0.5] * n, [R] * n)
+    plan.precompute()
+    for i, img in enumerate(imgs):
+        one = gpu_lib.precompute(torch.from_numpy(img).cuda(), sigma, scale=0.5, radius=R)
+        for a, b in zip(plan.maps_of(i).planes(), one.planes()):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("value", [np.inf, np.nan, 3e38])
 @pytest.mark.parametrize("R", [4, 12, 24])
 def test_maps_fp32_nonfinite_reach(gpu_lib, R, value):
@@ -168,7 +198,7 @@ def test_maps_fp32_nonfinite_reach(gpu_lib, R, value):
 
 
 @pytest.mark.parametrize("wdtype", [np.float32, np.float64], ids=["f32", "f64"])
-@pytest.mark.parametrize("R", [1, 5, 8, 16, 29, 32])
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 8, 16, 29, 32])
 def test_maps_fp32_nonfinite_rows(gpu_lib, R, wdtype):
     """Values that are not finite in several S_X row groups of a segment and between them: every pixel farther than R
     from all of them has the value of the weights without them, every other none in A; S_X has none."""
