@@ -272,7 +272,7 @@ def gpu_extras(dev, cases, itc, synth):
                                            c.M, itc._ptr(w0), c.iters, -1.0, itc._ptr(wout), itc._ptr(dtr),
                                            itc._ptr(dn), itc._stream()))
 
-        def run_wide():  # one launch per sweep over M / 32 workgroups
+        def run_wide():  # one launch per sweep over M / 8 workgroups
             conv()
             itc._check(lib.itc_lattice_fit_wide(itc.ctypes.byref(maps.desc), itc._ptr(maps.buf),
                                                 itc._ptr(maps.s_x), c.M, itc._ptr(w0), c.iters, -1.0,

@@ -211,8 +211,9 @@ itc_status itc_lattice_divergence_backward(const itc_lattice_desc* d, const void
  *            weight_scale = 1/a.
  * Requires 1 <= a <= b <= 2a, a <= ITC_MAX_CHAMFER_STEP,
  * width <= ITC_MAX_CHAMFER_WIDTH and height <= ITC_MAX_CHAMFER_HEIGHT.
- * t_out is also the intermediate of the two passes. Asynchronous on
- * `stream`; no allocation.
+ * t_out also holds what the kernels pass on to each other (the edges of its
+ * bands of rows, or the column distances). Asynchronous on `stream`; no
+ * allocation.
  */
 itc_status itc_lattice_chamfer(const itc_lattice_desc* d, const void* x, int32_t a, int32_t b,
                                float* t_out, void* stream);
@@ -241,7 +242,8 @@ itc_status itc_lattice_chamfer(const itc_lattice_desc* d, const void* x, int32_t
  *   work         device scratch of itc_lattice_literal_work_bytes(d, M,
  *                omega, radius_omega) bytes, 256-byte aligned (overwritten).
  * The paper's experiments choose omega = sqrt(N/M)/2 and xi = omega/2.
- * Asynchronous on `stream`: 2 (iters + 2) launches, no allocation.
+ * Asynchronous on `stream`: the convolution for P, a set-up launch and
+ * iters + 2 sweep launches, no allocation.
  */
 size_t itc_lattice_literal_work_bytes(const itc_lattice_desc* d, int32_t M, double omega,
                                       int32_t radius_omega);
@@ -375,8 +377,8 @@ itc_status itc_volume_fit(const itc_volume_desc* d, const void* maps, const doub
 /* ------------------------------------------------------------------------
  * Batched form: n independent images of uneven size, each with its own M,
  * sigma and iteration count, in flat device buffers. A plan is built once per
- * batch layout; its calls launch one persistent kernel each (convolution
- * over a cost-sorted tile queue; fit over a cost-sorted image queue) and
+ * batch layout; its calls launch a few persistent kernels each (convolution
+ * over cost-sorted tile queues; fit over one cost-sorted image queue) and
  * contain no allocation, synchronisation or memset, so they can be captured
  * into a HIP graph. Results are bitwise identical to the per-image calls on
  * the same stored images (the same convolution kernel is chosen when the
@@ -399,8 +401,8 @@ typedef struct {
 itc_status itc_lattice_plan_create(const itc_batch* b, itc_plan** out);
 
 /*
- * Convolution maps and S_X partials of every image: one persistent launch
- * per radius class. 8-bit images whose weight_off and pitch are multiples of
+ * Convolution maps and S_X partials of every image, in
+ * itc_lattice_plan_conv_launches(p) launches. 8-bit images whose weight_off and pitch are multiples of
  * 4 take the FP16-split convolution; the weights base must then be 4-byte
  * aligned (ITC_E_ARG otherwise).
  */
@@ -448,7 +450,8 @@ itc_status itc_lattice_divergence_backward_batched(itc_plan* p, const void* maps
  * Chamfer transform (itc_lattice_chamfer) of every image of a plan whose
  * weights are ITC_U8. Image i is read at byte offset weight_off[i] of
  * `weights` and written at float offset weight_off[i] of `t_out` (the same
- * pitch), so t_out holds 4x the bytes of the weights buffer. Two launches.
+ * pitch), so t_out holds 4x the bytes of the weights buffer. At most three
+ * launches.
  */
 itc_status itc_lattice_chamfer_batched(itc_plan* p, const void* weights, int32_t a, int32_t b, float* t_out,
                                        void* stream);
@@ -470,8 +473,8 @@ int32_t itc_lattice_plan_size(const itc_plan* p);
  * strips cut into segments of about `seg_rows` rows. Each FP32 class (FP32 and
  * FP64 weights, unaligned 8-bit rows) runs one persistent launch with
  * `blocks_per_cu` workgroups per compute unit; the classes of aligned 8-bit
- * rows share one persistent launch, with the smallest `blocks_per_cu` set on
- * any of them. The maps do not depend on the shape (bitwise).
+ * rows share their launches (one, or one a group of images that is read ahead),
+ * with the smallest `blocks_per_cu` set on any of them. The maps do not depend on the shape (bitwise).
  *
  * itc_lattice_plan_conv_classes: number of classes, -1 if p is NULL.
  * itc_lattice_plan_conv_class: class c's key (stable identifier), current

@@ -1,7 +1,7 @@
 """Autotuner of the batched convolution's tile shapes.
 
-A plan's convolution (Section 3.1's convolutions over a batch) runs one
-persistent launch per radius class over 64-column strips cut into segments.
+A plan's convolution (Section 3.1's convolutions over a batch) runs
+persistent launches over 64-column strips cut into segments.
 The segment height trades the recomputed halo rows of every segment (2R per
 segment) against the number of tiles that balance the compute units, and
 the workgroups per compute unit trade latency hiding against the tail of the

@@ -41,10 +41,10 @@
 //      tile of a map is then one contiguous 1 KiB of its panel, written by a
 //      single 16-byte-per-lane non-temporal store; h*A is summed into an
 //      FP64 partial of S_X per SX_ROWS-row group.
-// A batch runs one persistent launch over the tiles of every radius class
-// (sorted by radius, then cost), each workgroup walking the tile sublist of
-// its XCD; a workgroup clears its shared memory when the radius of its next
-// tile differs from the last one's.
+// A batch (or a group of its images, read ahead) runs one persistent launch over
+// the tiles of every radius class (sorted by radius, then cost), each workgroup
+// walking the tile sublist of its XCD; a workgroup clears its shared memory when
+// the radius of its next tile differs from the last one's.
 #include <type_traits>
 #include <utility>
 

@@ -243,8 +243,8 @@ struct itc_plan {
 // class, or CONV_MX_CLASS + aligned radius for the matrix-core kernel), every
 // image's strips cut into segments of about the class's target height
 // (multiples of the S_X row group), sorted by cost, most expensive first. A
-// FP32 class is one persistent launch; the 8-bit classes share
-// one persistent launch, largest radius first (a workgroup then changes its
+// FP32 class is one persistent launch; the 8-bit classes share one (or one a
+// group that is read ahead), largest radius first (a workgroup then changes its
 // ring layout only a few times), with the fewest workgroups per compute unit
 // any of them asks for. Every launch's tiles are split into one sublist per
 // XCD: every segment row of an image (the strips whose input windows

@@ -27,8 +27,9 @@
 // A launch is a chain of latencies: everything the previous one left is loaded
 // at once, and 18 window values per lane are in flight (a wave reads four rows of
 // a panel, 256 contiguous bytes). 512^2, M = 100, omega = 13.2 (81 x 81
-// windows): 5.7 us per sweep, 3.3 of them the launch itself, against 13.4 in two
-// launches (9.5 for the sums, 3.9 for the update of one workgroup).
+// windows): 5.6 us per sweep launch in a queue (3.4 of them the launch itself; 7.0
+// under the profiler), against 13.4 in two launches (9.5 for the sums, 3.9 for the
+// update of one workgroup).
 #include "itc_device.h"
 
 namespace itc {

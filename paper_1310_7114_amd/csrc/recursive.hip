@@ -266,12 +266,12 @@ __global__ void __launch_bounds__(64) rec_maps_kernel(const double* __restrict__
 //     and writes A, M_u, M_v and S_X straight from the registers: M_u from the
 //     thread's own neighbours (the ends of the next segments through LDS), M_v
 //     from the lanes beside it. Half panels rather than whole ones (18 x 56
-//     threads, 47 us): a 2048-wide image then gives 257 workgroups instead of
-//     129, and a thread may use twice the registers, so nothing spills. Whole
+//     threads, 47 us): a 2048-wide image then gives 256 workgroups instead of
+//     128, and a thread may use twice the registers, so nothing spills. Whole
 //     panels are kept for images of one S_X row group (at most 64 rows), where a
 //     panel has one S_X slot.
-// 2048 x 2048 8-bit, sigma = 16: 50 us a call (rows 17, columns 31) against 177;
-// 64 x 100: 27 against 77. Bound by E1's way through the caches (42 MB out and in)
+// 2048 x 2048 8-bit, sigma = 16: 48 us a call, one queued after another (rows 16,
+// columns 31, S_X 4 under the profiler) against 177; 64 x 100: 27 against 77. Bound by E1's way through the caches (42 MB out and in)
 // and the maps' 50 MB, then by the chains of dependent FMAs.
 // ---------------------------------------------------------------------------
 // The column pass for COLS columns: threads, segments in groups.
